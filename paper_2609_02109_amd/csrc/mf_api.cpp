@@ -970,8 +970,19 @@ mf_status search_range(mf_problem *p, const mf_search_args *args, uint64_t lo, u
 constexpr uint64_t kFixedChunk = 1ull << 36;   // configurations per scan launch set
 constexpr uint32_t kFixedInnerMin = 256;       // inner configurations per block (unless the space is smaller)
 
+// Bounds each wave of a grid hands on: the best top_k prefixes lie spread over
+// the waves, so a wave holds about m = top_k / waves of them; m + 6 sqrt(m) + 4
+// are exceeded with probability below 1e-6 (then the general scan runs).
+int mitm_list(int grid, int top_k)
+{
+    const double m = 1.2 * top_k / (16.0 * grid);
+    return (int)std::min(63.0, std::ceil(m + 6.0 * std::sqrt(m) + 4.0));
+}
+// [grid * 16][list + 1]: at most 24,576 keys over all grids and top_k
+constexpr size_t kMitmListBytes = (size_t)kMitmMaxGrid * 16 * 8 * 8;
+
 struct FixedWs {
-    size_t res, rows, pens, prow, lists, counts, total;
+    size_t res, rows, pens, prow, lists, counts, mitm_lists, mitm_counts, ticket, total;
     int grid;
 };
 
@@ -1028,6 +1039,9 @@ FixedWs fixed_ws_layout(const mf_problem &p, int grid, int top_k)
     w.prow = o; o = align256(o + (size_t)p.sumK * 8);
     w.lists = o; o = align256(o + (size_t)grid * top_k * sizeof(K128));
     w.counts = o; o = align256(o + (size_t)grid * 16);
+    w.mitm_lists = o; o = align256(o + kMitmListBytes);
+    w.mitm_counts = o; o = align256(o + (size_t)kMitmMaxGrid * 32);
+    w.ticket = o; o = align256(o + 4);
     w.total = o;
     return w;
 }
@@ -1075,13 +1089,156 @@ FixedArgs fixed_base(const mf_problem *p, const mf_objective &objective, int top
     return a;
 }
 
+// ---- meet in the middle (whole blocks of prefixes, no per-configuration output)
+
+// The split: the shortest suffix that leaves at most 1,024 prefixes when it
+// holds at most 1,024 combinations (one workgroup, one prefix per lane), else
+// at most 2^18 prefixes (one per lane of the chip) when it holds at most
+// kMitmSuffixMax, else the longest one within kMitmSuffixMax.
+struct MitmSplit {
+    int j0;
+    uint32_t S, spad;
+    uint64_t prefixes;
+};
+
+MitmSplit mitm_split(const mf_problem &p)
+{
+    MitmSplit best{p.N, 1, 64, p.space};
+    uint64_t S = 1;
+    for (int j = p.N - 1; j >= 0; j--) {
+        S *= (uint64_t)p.K[j];
+        if (S > kMitmSuffixMax) break;
+        best.j0 = j;
+        best.S = (uint32_t)S;
+        best.prefixes = p.space / S;
+        // stop as soon as the prefixes are few enough, unless a longer suffix
+        // within 1,024 makes it a single workgroup's work
+        if (best.prefixes <= 1024) break;
+        if (best.prefixes <= (1u << 18) && (j == 0 || S * (uint64_t)p.K[j - 1] > 1024)) break;
+    }
+    while (best.spad < best.S) best.spad *= 2;
+    return best;
+}
+
+// The part common to the fixed-state and the static search: ranges of at most
+// kMitmPrefixMax prefixes.  *general is set when a launch leaves the range
+// [lo, hi) from the returned lo on to the general scan.
+mf_status search_mitm(mf_problem *p, const mf_objective &objective, int n_steps, uint64_t &lo, uint64_t hi, int top_k,
+                      const float *d_omega, const FixedRow *rows, const FixedPen *pens, char *ws_res, char *ws_lists,
+                      char *ws_counts, char *ws_ticket, hipStream_t s, const EventLease &ev, mf_result &acc,
+                      bool &general)
+{
+    const MitmSplit sp = mitm_split(*p);
+    general = false;
+    // LDS: the kernel's static part takes below 14 KiB
+    if (mitm_lds_bytes(n_steps, p->sumK, sp.spad, objective.kind != MF_OBJ_LINEAR) + 14336 > 163840) {
+        general = true;
+        return MF_OK;
+    }
+    MitmArgs a{};
+    a.n_models = p->N;
+    a.sumK = p->sumK;
+    a.j0 = sp.j0;
+    a.n_steps = n_steps;
+    a.top_k = top_k;
+    a.eq3 = objective.kind != MF_OBJ_LINEAR ? 1 : 0;
+    a.S = sp.S;
+    a.spad = sp.spad;
+    a.vram_cap = p->vram_cap;
+    for (int i = 0; i < p->N; i++) {
+        a.K[i] = p->K[i];
+        a.opt_off[i] = p->opt_off[i];
+        a.magic[i] = magic_for(p->K[i]);
+    }
+    a.row_model = p->d_row_model;
+    a.rows = rows;
+    a.pens = pens;
+    a.omega = d_omega;
+    a.res = reinterpret_cast<DevResult *>(ws_res);
+    a.wg_lists = reinterpret_cast<unsigned long long *>(ws_lists);
+    a.wg_counts = reinterpret_cast<unsigned long long *>(ws_counts);
+    a.ticket = reinterpret_cast<uint32_t *>(ws_ticket);
+    a.res_host = ev.host_result();
+    while (lo < hi) {
+        // [lo, end): whole prefixes, but for the range's own ends
+        a.prefix0 = lo / sp.S;
+        const uint64_t last = std::min<uint64_t>((hi - 1) / sp.S, a.prefix0 + kMitmPrefixMax - 1);
+        const uint64_t end = std::min<uint64_t>(hi, (last + 1) * sp.S);
+        const uint32_t np = (uint32_t)(last - a.prefix0 + 1);
+        const uint32_t u_lo = (uint32_t)(lo - a.prefix0 * sp.S), u_hi = (uint32_t)(end - last * sp.S);
+        a.whole_lo = 0;
+        a.whole_hi = np;
+        for (int b = 0; b < 2; b++) a.part_prefix[b] = a.part_lo[b] = a.part_hi[b] = 0;
+        if (np == 1 && (u_lo != 0 || u_hi != sp.S)) {
+            a.whole_hi = 0;
+            a.part_lo[0] = u_lo;
+            a.part_hi[0] = u_hi;
+        } else {
+            if (u_lo != 0) {
+                a.whole_lo = 1;
+                a.part_lo[0] = u_lo;
+                a.part_hi[0] = sp.S;
+            }
+            if (u_hi != sp.S) {
+                a.whole_hi = np - 1;
+                a.part_prefix[1] = np - 1;
+                a.part_hi[1] = u_hi;
+            }
+        }
+        uint64_t x = a.prefix0;
+        for (int i = sp.j0 - 1; i >= 0; i--) {
+            a.base_digits[i] = (uint32_t)(x % (uint64_t)p->K[i]);
+            x /= (uint64_t)p->K[i];
+        }
+        const uint32_t whole = a.whole_hi - a.whole_lo;
+        // one workgroup up to four prefixes per lane (no second level of
+        // lists), else a prefix per lane up to one workgroup per CU
+        const int grid = whole <= 4096 ? 1 : (int)std::min<uint32_t>((whole + 1023) / 1024, (uint32_t)std::min(p->num_cus, kMitmMaxGrid));
+        a.list = mitm_list(grid, top_k);
+        a.seq = p->call_seq.fetch_add(1) + 1;
+        if (a.res_host) a.res_host->done_seq = 0;
+        if (launch_mitm(a, grid, s) != hipSuccess) return MF_EDEVICE;
+        DevResult h;
+        if (a.res_host) {
+            const mf_status st = wait_done(a.res_host, a.seq, s);
+            if (st != MF_OK) return st;
+            std::memcpy(&h, a.res_host, sizeof(h));
+        } else if (hipMemcpyAsync(&h, a.res, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
+                   hipStreamSynchronize(s) != hipSuccess) {
+            return MF_EDEVICE;
+        }
+        if (!(h.status & kStatVerified)) {
+            general = true;
+            return MF_OK;
+        }
+        mf_result part;
+        empty_result(part);
+        part.n_eval = end - lo;
+        part.n_vram = h.n_vram;
+        part.n_feas = h.n_feas_sure;
+        part.n_top = h.n_top;
+        for (int q = 0; q < h.n_top; q++) {
+            part.top_idx[q] = h.top_idx[q];
+            part.top_J[q] = h.top_J[q];
+        }
+        part.main_kernel_ms = (float)((double)h.fast_ticks / p->wall_khz);
+        merge_into(acc, part, top_k);
+        lo = end;
+    }
+    return MF_OK;
+}
+
 mf_status search_fixed(mf_problem *p, const mf_search_args *args, char *ws, hipStream_t s, const EventLease &ev,
                        mf_result &acc)
 {
     if (args->hi == args->lo) return MF_OK;
     const FixedWs w = fixed_ws_layout(*p, p->num_cus * kFixedMaxWgsPerCu, args->top_k);
-    FixedArgs a = fixed_base(p, args->objective, args->top_k);
-    for (int k = 0; k < p->A; k++) a.state[k] = args->state[k];
+    FixedTableArgs ta{};
+    FixedArgs &a = ta.f;
+    a = fixed_base(p, args->objective, args->top_k);
+    for (int k = 0; k < p->A; k++) ta.state[k] = args->state[k];
+    ta.n_steps = 1;
+    ta.ticket = reinterpret_cast<uint32_t *>(ws + w.ticket);
     a.sla = args->d_sla;
     a.omega = args->d_omega;
     a.rows = reinterpret_cast<FixedRow *>(ws + w.rows);
@@ -1091,10 +1248,19 @@ mf_status search_fixed(mf_problem *p, const mf_search_args *args, char *ws, hipS
     a.wg_counts = reinterpret_cast<unsigned long long *>(ws + w.counts);
     a.res = reinterpret_cast<DevResult *>(ws + w.res);
     const bool dump = (args->flags & MF_DUMP) != 0;
+    if (launch_fixed_table(ta, s) != hipSuccess) return MF_EDEVICE;
+    uint64_t lo = args->lo;
+    if (!dump) {
+        bool general;
+        const mf_status st = search_mitm(p, args->objective, 1, lo, args->hi, args->top_k, args->d_omega, a.rows,
+                                         a.pens, ws + w.res, ws + w.mitm_lists, ws + w.mitm_counts, ws + w.ticket, s,
+                                         ev, acc, general);
+        if (st != MF_OK || !general) return st;
+    }
 
     hipEvent_t ev0 = ev.start(), ev1 = ev.stop();
     mf_status st = MF_OK;
-    for (uint64_t lo = args->lo; lo < args->hi;) {
+    while (lo < args->hi) {
         const uint64_t n = std::min<uint64_t>(args->hi - lo, kFixedChunk);
         a.lo = lo;
         a.n = n;
@@ -1114,7 +1280,7 @@ mf_status search_fixed(mf_problem *p, const mf_search_args *args, char *ws, hipS
         DevResult h{};
         float ms = 0.f;
         if (hipMemsetAsync(a.res, 0, sizeof(DevResult), s) != hipSuccess ||
-            launch_fixed(a, grid, lo == args->lo, s, ev0, ev1) != hipSuccess ||
+            launch_fixed(a, grid, s, ev0, ev1) != hipSuccess ||
             hipMemcpyAsync(&h, a.res, sizeof(DevResult), hipMemcpyDeviceToHost, s) != hipSuccess ||
             hipStreamSynchronize(s) != hipSuccess ||
             (ev0 && hipEventElapsedTime(&ms, ev0, ev1) != hipSuccess)) {
@@ -1142,7 +1308,7 @@ mf_status search_fixed(mf_problem *p, const mf_search_args *args, char *ws, hipS
 // ---- static (multi-step) search
 
 struct StaticWs {
-    size_t res, rows, pens, prow, lists, counts, total;
+    size_t res, rows, pens, prow, lists, counts, mitm_lists, mitm_counts, ticket, total;
 };
 
 StaticWs static_ws_layout(const mf_problem &p, int n_steps, int top_k)
@@ -1156,6 +1322,9 @@ StaticWs static_ws_layout(const mf_problem &p, int n_steps, int top_k)
     w.prow = o; o = align256(o + (size_t)p.sumK * 8);
     w.lists = o; o = align256(o + (size_t)p.num_cus * kFixedMaxWgsPerCu * top_k * sizeof(K128));
     w.counts = o; o = align256(o + (size_t)p.num_cus * kFixedMaxWgsPerCu * 16);
+    w.mitm_lists = o; o = align256(o + kMitmListBytes);
+    w.mitm_counts = o; o = align256(o + (size_t)kMitmMaxGrid * 32);
+    w.ticket = o; o = align256(o + 4);
     w.total = o;
     return w;
 }
@@ -1200,33 +1369,29 @@ mf_status check_static_args(const mf_problem *p, const mf_static_args *a, bool s
 
 // Per-step tables: step t's observed state, bounds and previous deployment
 // (the objective's at step 0, none afterwards: the configuration is its own).
-mf_status static_setup(mf_problem *p, const mf_static_args *args, char *ws, int top_k, hipStream_t s, StaticArgs &sa)
+mf_status static_setup(mf_problem *p, const mf_static_args *args, char *ws, const StaticWs &w, int top_k,
+                       hipStream_t s, StaticArgs &sa)
 {
-    const StaticWs w = static_ws_layout(*p, args->n_steps, top_k);
-    FixedArgs a = fixed_base(p, args->objective, top_k);
-    a.rows = nullptr;
+    FixedTableArgs ta{};
+    FixedArgs &a = ta.f;
+    a = fixed_base(p, args->objective, top_k);
     a.pred_rows = reinterpret_cast<float2 *>(ws + w.prow);
     a.wg_lists = reinterpret_cast<K128 *>(ws + w.lists);
     a.wg_counts = reinterpret_cast<unsigned long long *>(ws + w.counts);
     a.res = reinterpret_cast<DevResult *>(ws + w.res);
+    a.sla = args->d_sla;
+    a.omega = args->d_omega;
     sa = StaticArgs{};
     sa.n_steps = args->n_steps;
     sa.omega_steps = args->d_omega;
     sa.rows_steps = reinterpret_cast<FixedRow *>(ws + w.rows);
     sa.pens_steps = reinterpret_cast<FixedPen *>(ws + w.pens);
-    for (int t = 0; t < args->n_steps; t++) {
-        FixedArgs ft = a;
-        for (int k = 0; k < p->A; k++) ft.state[k] = args->h_state[(size_t)t * p->A + k];
-        ft.sla = args->d_sla + (size_t)t * p->N;
-        ft.omega = args->d_omega + (size_t)t * p->N;
-        ft.rows = sa.rows_steps + (size_t)t * p->sumK;
-        ft.pens = sa.pens_steps + (size_t)t * p->sumK;
-        if (t > 0)
-            for (int i = 0; i < kMaxN; i++) ft.obj.prev[i] = -1;
-        if (launch_fixed_table(ft, s) != hipSuccess) return MF_EDEVICE;
-    }
-    a.sla = args->d_sla;
-    a.omega = args->d_omega;
+    a.rows = sa.rows_steps;
+    a.pens = sa.pens_steps;
+    ta.n_steps = args->n_steps;
+    ta.ticket = reinterpret_cast<uint32_t *>(ws + w.ticket);
+    std::memcpy(ta.state, args->h_state, sizeof(float) * (size_t)args->n_steps * p->A);
+    if (launch_fixed_table(ta, s) != hipSuccess) return MF_EDEVICE;
     sa.f = a;
     return MF_OK;
 }
@@ -1235,12 +1400,21 @@ mf_status search_static(mf_problem *p, const mf_static_args *args, char *ws, hip
 {
     if (args->hi == args->lo) return MF_OK;
     StaticArgs sa;
-    mf_status st = static_setup(p, args, ws, args->top_k, s, sa);
+    const StaticWs w = static_ws_layout(*p, args->n_steps, args->top_k);
+    mf_status st = static_setup(p, args, ws, w, args->top_k, s, sa);
     if (st != MF_OK) return st;
-    const int wgs_per_cu = static_wgs_per_cu(sa);
     const EventLease ev(p, true);
+    uint64_t lo = args->lo;
+    if (!args->d_mask) {
+        bool general;
+        st = search_mitm(p, args->objective, args->n_steps, lo, args->hi, args->top_k, args->d_omega, sa.rows_steps,
+                         sa.pens_steps, ws + w.res, ws + w.mitm_lists, ws + w.mitm_counts, ws + w.ticket, s, ev, acc,
+                         general);
+        if (st != MF_OK || !general) return st;
+    }
+    const int wgs_per_cu = static_wgs_per_cu(sa);
     hipEvent_t ev0 = ev.start(), ev1 = ev.stop();
-    for (uint64_t lo = args->lo; lo < args->hi;) {
+    while (lo < args->hi) {
         const uint64_t n = std::min<uint64_t>(args->hi - lo, kFixedChunk);
         FixedArgs &a = sa.f;
         a.lo = lo;
@@ -1950,7 +2124,7 @@ mf_status mf_eval_static(mf_problem *p, const mf_static_args *args, const uint64
     if (n == 0) return MF_OK;
     hipStream_t s = (hipStream_t)stream;
     StaticArgs sa;
-    st = static_setup(p, args, (char *)d_ws, 1, s, sa);
+    st = static_setup(p, args, (char *)d_ws, static_ws_layout(*p, args->n_steps, 1), 1, s, sa);
     if (st != MF_OK) return st;
     sa.idx = d_idx;
     sa.n_list = n;

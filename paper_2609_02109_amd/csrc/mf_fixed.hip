@@ -12,54 +12,93 @@
 // outer part of the chain (J, VRAM sum, service flag) is computed once, and
 // each lane adds the inner models of its own configuration (two LDS rows per
 // configuration at the usual shapes).  Top-k are selected on 128-bit (J,
-// index) keys, per wave, per workgroup, then over the grid.
+// index) keys, per wave, per workgroup, then over the grid.  Without a dump
+// the scan runs only where the meet-in-the-middle search (mf_mitm.hip) leaves
+// a range to it.
 #include "mf_canon.h"
 
 namespace mfi {
 
 // ---------------------------------------------------------------------------
-// Table: one 64-thread workgroup per option row.
+// Table: one workgroup of NT threads per option row and step, a thread per
+// hidden unit (NT = 64, 128 or 256).  Bound by the latency of each unit's
+// dependent fma chain and its weight loads: 32 weights are loaded ahead of
+// their chain steps (8 before: 31 us for the 128 rows of 40-256-256-2, one
+// wave taking four units per lane), and layer 3's weights while layer 1 runs.
 // ---------------------------------------------------------------------------
-template <bool BF16>
-__global__ void __launch_bounds__(64) fixed_table_kernel(const FixedArgs a)
+template <bool BF16, int NT>
+__global__ void __launch_bounds__(NT) fixed_table_kernel(const FixedTableArgs ta)
 {
+    const FixedArgs &a = ta.f;
     __shared__ double h1s[kCanonMaxH];
     __shared__ double h2s[kCanonMaxH];
     __shared__ double zs[kCanonMaxIn];
+    __shared__ float w3s[2 * kCanonMaxH + 2];
     __shared__ float s_tau[kMaxN];
     __shared__ int32_t s_prev[kMaxN];
-    const int lane = threadIdx.x;
+    const int tid = threadIdx.x, r = blockIdx.x, t = blockIdx.y;
+    if (ta.ticket && tid == 0 && r == 0 && t == 0) *ta.ticket = 0u;
 #pragma unroll
     for (int i = 0; i < kMaxN; i++)   // compile-time index into the argument block
-        if (lane == i) {
+        if (tid == i) {
             s_tau[i] = a.obj.tau[i];
-            s_prev[i] = a.obj.prev[i];
+            s_prev[i] = t == 0 ? a.obj.prev[i] : -1;
         }
-    const int nin = a.L + a.A;
-    for (int r = blockIdx.x; r < a.sumK; r += gridDim.x) {
-        const int i = a.row_model[r];
-        const float *x = a.features + (int64_t)r * a.L;
-        __syncthreads();
-        for (int k = lane; k < nin; k += 64) zs[k] = k < a.L ? (double)x[k] : (double)a.state[k - a.L];
-        __syncthreads();
-        double lat, thr;
-        canon_model<BF16>(a.weights + (int64_t)i * a.wstride, nin, a.H1, a.H2, zs, h1s, h2s, lane, lat, thr, a.act);
-        if (lane == 0) {
-            FixedRow row;
-            FixedPen pp = {0.0, 0.0};
-            uint32_t fl = lat <= (double)a.sla[i] ? 0u : kRowBad;
-            row.q = thr;
-            if (a.obj.kind != 0) {
-                bool do_P, do_pen;
-                if (!canon_eq3(a.obj, r, thr, s_tau[i], s_prev[i], row.q, pp.P, do_P, pp.pen, do_pen)) fl = kRowBad;
-                fl |= (do_P ? kRowP : 0u) | (do_pen ? kRowPen : 0u);
-            }
-            row.vram = x[a.vram_col];
-            row.flags = fl;
-            a.rows[r] = row;
-            a.pens[r] = pp;
-            a.pred_rows[r] = make_float2((float)lat, (float)thr);
+    const int nin = a.L + a.A, H1 = a.H1, H2 = a.H2;
+    const int i = a.row_model[r];
+    const float *x = a.features + (int64_t)r * a.L;
+    const float *W1T = a.weights + (int64_t)i * a.wstride, *b1 = W1T + (int64_t)nin * H1, *W2T = b1 + H1,
+                *b2 = W2T + (int64_t)H1 * H2, *W3 = b2 + H2;
+    for (int k = tid; k < nin; k += NT)
+        zs[k] = k < a.L ? (double)x[k] : (double)ta.state[t * a.A + (k - a.L)];
+    for (int k = tid; k < 2 * H2 + 2; k += NT) w3s[k] = W3[k];   // W3[2][H2], b3[2]
+    __syncthreads();
+    for (int u = tid; u < H1; u += NT) {
+        if (BF16) {
+            float c = b1[u];
+#pragma unroll 32
+            for (int k = 0; k < nin; k++) c = fmaf(W1T[(int64_t)k * H1 + u], (float)zs[k], c);
+            c = c > 0.f ? c : 0.f;
+            h1s[u] = bf16_round_d((double)c);
+        } else {
+            double c = (double)b1[u];
+#pragma unroll 32
+            for (int k = 0; k < nin; k++) c = fma((double)W1T[(int64_t)k * H1 + u], zs[k], c);
+            h1s[u] = c > 0.0 ? c : 0.0;
         }
+    }
+    __syncthreads();
+    for (int v = tid; v < H2; v += NT) {
+        double c = (double)b2[v];
+#pragma unroll 32
+        for (int u = 0; u < H1; u++) c = fma((double)W2T[(int64_t)u * H2 + v], h1s[u], c);
+        h2s[v] = c > 0.0 ? c : 0.0;
+    }
+    __syncthreads();
+    if (tid >= 64) return;
+    double y = 0.0;
+    if (tid < 2) {
+        double c = (double)w3s[2 * H2 + tid];
+#pragma unroll 16
+        for (int v = 0; v < H2; v++) c = fma((double)w3s[tid * H2 + v], h2s[v], c);
+        y = a.act ? canon_sigmoid(c) : c;
+    }
+    const double lat = __shfl(y, 0), thr = __shfl(y, 1);
+    if (tid == 0) {
+        FixedRow row;
+        FixedPen pp = {0.0, 0.0};
+        uint32_t fl = lat <= (double)a.sla[(int64_t)t * a.n_models + i] ? 0u : kRowBad;
+        row.q = thr;
+        if (a.obj.kind != 0) {
+            bool do_P, do_pen;
+            if (!canon_eq3(a.obj, r, thr, s_tau[i], s_prev[i], row.q, pp.P, do_P, pp.pen, do_pen)) fl = kRowBad;
+            fl |= (do_P ? kRowP : 0u) | (do_pen ? kRowPen : 0u);
+        }
+        row.vram = x[a.vram_col];
+        row.flags = fl;
+        a.rows[(int64_t)t * a.sumK + r] = row;
+        a.pens[(int64_t)t * a.sumK + r] = pp;
+        if (t == 0) a.pred_rows[r] = make_float2((float)lat, (float)thr);
     }
 }
 
@@ -758,10 +797,9 @@ int fixed_wgs_per_cu(const FixedArgs &a)
     return n < kFixedMaxWgsPerCu ? n : kFixedMaxWgsPerCu;
 }
 
-hipError_t launch_fixed(const FixedArgs &a, int grid, bool table, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
+hipError_t launch_fixed(const FixedArgs &a, int grid, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
 {
     hipError_t e;
-    if (table && (e = launch_fixed_table(a, s)) != hipSuccess) return e;
     const size_t lds = fixed_lds_bytes(a.sumK, a.obj.kind != 0);
     const ScanFn fn = scan_fn(a);
     e = ensure_dyn_lds((const void *)fn, lds);
@@ -1026,12 +1064,15 @@ int static_wgs_per_cu(const StaticArgs &a)
     return n < kFixedMaxWgsPerCu ? n : kFixedMaxWgsPerCu;
 }
 
-hipError_t launch_fixed_table(const FixedArgs &a, hipStream_t s)
+hipError_t launch_fixed_table(const FixedTableArgs &a, hipStream_t s)
 {
-    if (a.bf16)
-        hipLaunchKernelGGL(fixed_table_kernel<true>, dim3(a.sumK), dim3(64), 0, s, a);
-    else
-        hipLaunchKernelGGL(fixed_table_kernel<false>, dim3(a.sumK), dim3(64), 0, s, a);
+    const int h = a.f.H1 > a.f.H2 ? a.f.H1 : a.f.H2;
+    const int nt = h <= 64 ? 64 : (h <= 128 ? 128 : 256);
+    auto fn = a.f.bf16 ? (nt == 64 ? fixed_table_kernel<true, 64>
+                                   : (nt == 128 ? fixed_table_kernel<true, 128> : fixed_table_kernel<true, 256>))
+                       : (nt == 64 ? fixed_table_kernel<false, 64>
+                                   : (nt == 128 ? fixed_table_kernel<false, 128> : fixed_table_kernel<false, 256>));
+    hipLaunchKernelGGL(fn, dim3(a.f.sumK, a.n_steps), dim3(nt), 0, s, a);
     return hipGetLastError();
 }
 

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "../../include/mf.h"
+#include "mf_vram.h"
 
 namespace mfi {
 
@@ -418,6 +419,45 @@ struct StaticArgs {
     uint32_t *out_flags;             // [n][T] or null
 };
 
+// Per-row tables of one or more steps in one launch (fixed_table_kernel):
+// step t takes state[t][A], the latency bounds f.sla + t N, and writes
+// f.rows + t sumK (f.pens likewise); its previous deployment is f.obj.prev
+// at step 0 and none afterwards.  ticket (optional) is zeroed.
+struct FixedTableArgs {
+    FixedArgs f;
+    int n_steps;
+    uint32_t *ticket;
+    float state[MF_MAX_STEPS * MF_MAX_AGG];
+};
+
+// A separable search by meet in the middle (mf_mitm.hip): prefix = models
+// 0 .. j0 - 1, suffix = the rest (S combinations, spad the next power of
+// two).  Prefixes are counted from prefix0 (its digits in base_digits);
+// [whole_lo, whole_hi) lie in the range with every suffix, part_prefix[b]
+// with the suffixes [part_lo[b], part_hi[b]).
+constexpr uint32_t kMitmSuffixMax = 4096;       // suffixes sorted in LDS
+constexpr int kMitmMaxGrid = 256;               // workgroups of a launch at most
+constexpr uint32_t kMitmPrefixMax = 1u << 23;   // prefixes per launch (24-bit keys, exact magic quotients)
+struct MitmArgs {
+    int n_models, sumK, j0, n_steps, top_k, list, eq3;   // list: bounds a wave of a grid hands on (< 64)
+    int32_t K[kMaxN];
+    int32_t opt_off[kMaxN];
+    uint32_t magic[kMaxN], base_digits[kMaxN];
+    uint32_t S, spad, whole_lo, whole_hi;
+    uint32_t part_prefix[2], part_lo[2], part_hi[2];
+    uint64_t prefix0;
+    float vram_cap;
+    const int32_t *row_model;
+    const FixedRow *rows;                 // [n_steps][sumK]
+    const FixedPen *pens;                 // [n_steps][sumK]
+    const float *omega;                   // [n_steps][n_models]
+    unsigned long long *wg_lists;         // [grid * 16 waves][list + 1]
+    unsigned long long *wg_counts;        // [grid][4]: VRAM-feasible, feasible, start tick, -
+    uint32_t *ticket;                     // zero before the launch, zero after it
+    DevResult *res, *res_host;            // res_host: optional, pinned host memory
+    unsigned long long seq;
+};
+
 // GA problem constants (kernel-argument block).
 struct GAConst {
     int N, L, A, H1, H2, bf16, act;
@@ -487,12 +527,14 @@ size_t fast_small_epilogue_bytes(int n_models);
 constexpr uint64_t kSmallRange = 1ull << 20;   // fp32 ranges up to this size finish in one workgroup
 size_t fixed_lds_bytes(int sumK, bool eq3);
 size_t static_lds_bytes(int n_steps, int sumK, int n_models, bool eq3);
-hipError_t launch_fixed_table(const FixedArgs &a, hipStream_t s);
+hipError_t launch_fixed_table(const FixedTableArgs &a, hipStream_t s);
+size_t mitm_lds_bytes(int n_steps, int sumK, uint32_t spad, bool eq3);
+hipError_t launch_mitm(const MitmArgs &a, int grid, hipStream_t s);
 hipError_t launch_static(const StaticArgs &a, int grid, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_static_eval(const StaticArgs &a, hipStream_t s);
 int static_wgs_per_cu(const StaticArgs &a);
 int fixed_wgs_per_cu(const FixedArgs &a);
-hipError_t launch_fixed(const FixedArgs &a, int grid, bool table, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
+hipError_t launch_fixed(const FixedArgs &a, int grid, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 constexpr int64_t kGaWideMax = 8192;   // populations (S x P) up to this size take the wide fitness kernel
 constexpr int kSelParts = 128;            // workgroups of the two-level selection over long entry lists
 constexpr uint64_t kSelSingleMax = 1ull << 20;   // ranges up to this size select in one workgroup

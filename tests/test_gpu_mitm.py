@@ -1,0 +1,168 @@
+"""The separable searches by meet in the middle (fixed-state and static,
+without a dump) against the general scan of the same library (the same call
+with a dump, which the oracle pins elsewhere): counts, top-k indices and
+canonical J bit for bit, over the splits, ranges and values where the two
+could differ.  The inversion of the rounded VRAM additions is checked on the
+CPU against the additions themselves."""
+import os
+import subprocess
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+from paper_2609_02109_amd import synth
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def mf():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_02109_amd import mf as mfmod
+    return mfmod
+
+
+INVERSE_TEST = r"""
+#include <cstdio>
+#include <cstdint>
+#include <cstring>
+#include <random>
+#include "mf_vram.h"
+static float bits(uint32_t b) { float f; memcpy(&f, &b, 4); return f; }
+int main()
+{
+    std::mt19937_64 r(1);
+    long bad = 0;
+    for (long t = 0; t < 20000000; t++) {
+        float thr, v;
+        const int kind = t % 5;
+        if (kind == 0) {                       // any finite bit patterns
+            do thr = bits((uint32_t)r()); while (!std::isfinite(thr));
+            do v = bits((uint32_t)r()); while (!std::isfinite(v));
+        } else if (kind == 1) {                // VRAM-like
+            thr = (float)(r() % 4000000) * 0x1p-14f;
+            v = (float)(r() % 700000) * 0x1p-14f;
+        } else if (kind == 2) {                // off the grid, mixed sign
+            thr = 300.f * (float)((double)r() * 0x1p-64 - 0.3);
+            v = 40.f * (float)((double)r() * 0x1p-64 - 0.5);
+        } else if (kind == 3) {                // cancelling, within a few units of each other
+            v = 100.f * (float)((double)r() * 0x1p-64);
+            thr = v;
+            for (int i = (int)(r() % 5); i > 0; i--) thr = nextafterf(thr, (r() & 1) ? INFINITY : -INFINITY);
+        } else {                               // extremes
+            const float e[] = {FLT_MAX, -FLT_MAX, FLT_MIN, -FLT_MIN, 0x1p-149f, -0x1p-149f, 0.f, -0.f, 1.f, 0x1p100f, -INFINITY};
+            thr = e[r() % 11];
+            v = e[r() % 10];
+        }
+        const float x = mfi::vram_inverse(thr, v);
+        bool ok = true;
+        volatile float s;
+        if (x > -INFINITY) { s = x + v; ok = ok && s <= thr; }
+        if (x < FLT_MAX) { const float y = nextafterf(x, INFINITY); s = y + v; ok = ok && !(s <= thr); }
+        if (!ok && ++bad < 10) printf("thr %a v %a x %a\n", thr, v, x);
+    }
+    printf("bad %ld\n", bad);
+    return bad != 0;
+}
+"""
+
+
+def test_vram_inverse_cpu(tmp_path):
+    src, exe = tmp_path / "inv.cpp", tmp_path / "inv"
+    src.write_text(INVERSE_TEST)
+    inc = os.path.join(ROOT, "paper_2609_02109_amd", "csrc")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-ffp-contract=off", f"-I{inc}", str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
+def same(a, b):
+    assert a["n_eval"] == b["n_eval"] and a["n_vram"] == b["n_vram"] and a["n_feas"] == b["n_feas"]
+    np.testing.assert_array_equal(a["top_idx"], b["top_idx"])
+    assert a["top_J"].tobytes() == b["top_J"].tobytes()
+
+
+def instance(n_options, seed=0, edit=None, **kw):
+    kw.setdefault("vram_quantile", 0.6)
+    inst = synth.make_instance(n_options, 8, 4, 32, 32, seed=seed, quantise=False, sla_range=(0.2, 1.0), **kw)
+    if edit is not None:
+        edit(inst)
+    return inst
+
+
+def negative_vram(inst):
+    inst.features[:, synth.COL_VRAM] -= 15.0
+
+
+def huge_vram(inst):   # sums that overflow to infinity
+    inst.features[::3, synth.COL_VRAM] = 3e38
+
+
+def tied(inst):        # every configuration's J equal
+    for i in range(inst.n_models):
+        W1, b1, W2, b2, W3, b3 = inst.model_weights(i)
+        W3[1, :] = 0.0
+
+
+# one model; the largest option count; single options; suffixes of exactly
+# 64, 4,096 and just past; one workgroup and many; more than eight models
+SHAPES = [([5], None), ([255], None), ([3, 1, 1, 5], None), ([2] * 6, None), ([2] * 12, None), ([2] * 13, None),
+          ([63, 65], None), ([255, 20], None), ([7, 11, 5, 9], negative_vram), ([9, 8, 7, 6], huge_vram),
+          ([9, 10, 8], tied), ([13, 16, 16, 17], None), ([4] * 9, None), ([24, 24, 24, 24], None), ([130, 131], None)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_options,edit", SHAPES, ids=[f"{'x'.join(map(str, s))}{'-' + e.__name__ if e else ''}" for s, e in SHAPES])
+@pytest.mark.parametrize("eq3", [False, True])
+def test_mitm_matches_general_scan(mf, n_options, edit, eq3):
+    inst = instance(n_options, edit=edit, vram_cap=90.0 if edit is huge_vram else None)
+    n = inst.space_size
+    ob = synth.make_objective(inst, 3, tau_range=(-0.4, 0.3)) if eq3 else None
+    st = synth.make_state(instance(n_options), 5)
+    p = mf.Problem(inst, variants=ob)
+    for lo, hi in {(0, n), (n // 3, n), (1, max(n - 1, 1)), (n // 2, min(n // 2 + 3, n)), (0, max(2 * n // 3, 1))}:
+        for k in (1, 33, 64):
+            print(f"[mitm] {n_options} eq3={eq3} [{lo},{hi}) k={k}", flush=True)
+            a = p.search(inst.sla, inst.omega, k=k, lo=lo, hi=hi, objective=ob, state=st)
+            b = p.search(inst.sla, inst.omega, k=k, lo=lo, hi=hi, objective=ob, state=st, dump=True)
+            same(a, b)
+    p.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("omega", [np.array([1, -2, 0, 0.5, 1], np.float32), np.full(5, 1e30, np.float32)])
+def test_mitm_cap_equal_to_a_sum_and_weights(mf, omega):
+    # an inclusive cap that some configurations' rounded sums equal, weights of
+    # either sign and of a size whose slack is large against J's differences
+    inst = instance([12, 7, 9, 9, 5], seed=2)
+    d = [3, 2, 5, 7, 1]
+    v = np.float32(0)
+    for i in range(5):
+        v = np.float32(v + inst.features[inst.option_offsets[i] + d[i], synth.COL_VRAM])
+    st = synth.make_state(inst, 1)
+    for cap in (v, np.nextafter(v, np.float32(0))):
+        p = mf.Problem(replace(inst, vram_cap=float(cap)))
+        a = p.search(inst.sla, omega, k=16, state=st)
+        same(a, p.search(inst.sla, omega, k=16, state=st, dump=True))
+        p.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_options", [[12, 12, 9, 9, 9], [5, 4, 3], [6, 7, 8, 9, 10, 5]])
+@pytest.mark.parametrize("steps", [1, 2, 17])
+def test_mitm_static_matches_general_scan(mf, n_options, steps):
+    inst = synth.make_instance(n_options, 8, 4, 64, 32, seed=4, vram_quantile=0.7, act="sigmoid", quantise=False)
+    ob = synth.make_objective(inst, 4)
+    sc = synth.make_scenarios(inst, 1, steps, seed=4)
+    n = inst.space_size
+    p = mf.Problem(inst, variants=ob)
+    for lo, hi in ((0, n), (5, n - 2), (n // 2 + 1, n // 2 + 4)):
+        for k in (1, 40):
+            print(f"[mitm static] {n_options} T={steps} [{lo},{hi}) k={k}", flush=True)
+            args = (sc.states[0], sc.sla[0], sc.omega[0])
+            a = p.search_static(*args, k=k, lo=lo, hi=hi, objective=ob)
+            same(a, p.search_static(*args, k=k, lo=lo, hi=hi, objective=ob, dump=True))
+    p.close()

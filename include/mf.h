@@ -358,13 +358,17 @@ typedef struct {
     uint32_t flags;            /* MF_FIXED_STATE: the surrogates see state[] (as in mf_search) */
     float state[MF_MAX_AGG];   /* MF_FIXED_STATE: observed aggregate, original slot order, finite */
     mf_objective objective;    /* zero-initialised: MF_OBJ_LINEAR; MF_OBJ_EQ3 as in mf_search */
-    /* Optional host output (NULL: none): the individuals of the run whose
-     * fitness ran the surrogates.  Large populations (S x pop > 8192, shapes
-     * with the one-lane fitness kernel) over joint spaces small enough to
-     * tabulate (|Lambda| (16 N + 4) bytes <= 256 MiB) keep a memo of each
-     * evaluated index's canonical predictions in the workspace for the rest of
-     * the run; later generations read it (the values, and so the trajectory,
-     * are the same).  Otherwise every individual counts. */
+    /* Optional host output (NULL: none): the surrogate evaluations of the run,
+     * in configurations.  Runs whose individuals outnumber the joint space (and
+     * whose space has at most 32,768 configurations per generation and 1 GiB of
+     * fitness over the scenarios, at the shapes of the one-lane kernel) evaluate every
+     * VRAM-feasible configuration first: their number.
+     * Otherwise large populations (S x pop > 8192, the same shapes, |Lambda|
+     * (16 N + 4) bytes <= 256 MiB) keep a memo of each evaluated index's
+     * predictions in the workspace for the rest of the run: the individuals
+     * that were not in it.  The values, and so the trajectory, are the same
+     * each way.  Otherwise every individual counts (under MF_FIXED_STATE too,
+     * where the predictions come from a table of the option rows). */
     uint64_t *h_forwards;
 } mf_ga_args;
 

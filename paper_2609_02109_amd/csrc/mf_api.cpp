@@ -2209,9 +2209,19 @@ static mf_status check_ga_args(const mf_problem *p, const mf_ga_args *a)
 }
 
 struct GaWs {
-    size_t cnt, off, nfl, fl, popA, popB, fit, bJ, bI, memo, tag, nfwd, total;
+    size_t cnt, off, nfl, fl, popA, popB, fit, bJ, bI, memo, tag, nfwd, recs, lt, table_at, total;
     bool use_memo;
+    bool run;        // whole generations in one launch (ga_run_kernel)
+    bool table;      // ... on the predictions of every feasible configuration
+    int span;        // ... this many generations of draws at a time
 };
+
+// Tabulating every feasible configuration costs about 0.9 ns each (the whole
+// chip evaluating; 12-32-32-2, N = 5), a generation in two launches about
+// 30 us more than one inside the run kernel: worth it up to this many
+// configurations per generation, and while the run evaluates that many
+// individuals at all.
+constexpr uint64_t kGaTablePerGen = 32768;
 
 // The GAConst of a run without its device pointers' workspace parts (the
 // shape fields the kernels' choices depend on).
@@ -2221,6 +2231,7 @@ static GAConst ga_shape(const mf_problem *p)
     c.N = p->N; c.L = p->L; c.A = p->A; c.H1 = p->H1; c.H2 = p->H2; c.bf16 = p->bf16; c.act = p->act;
     c.pre = p->d_pre;
     c.sumK = p->sumK;
+    c.wstride = p->wstride;
     return c;
 }
 
@@ -2242,10 +2253,29 @@ static GaWs ga_ws(const mf_problem *p, const mf_ga_args *a)
     // the run's memo of canonical predictions per joint index (large
     // populations over spaces small enough to tabulate)
     const uint64_t memo_bytes = p->space * (uint64_t)p->N * 16u + p->space * 4u;
-    w.use_memo = ga_memo_supported(ga_shape(p), a->n_scen, a->pop) && memo_bytes <= kGaMemoMaxBytes;
-    w.memo = o; o = align256(o + (w.use_memo ? p->space * (size_t)p->N * 16 : 0));
-    w.tag = o; o = align256(o + (w.use_memo ? p->space * 4 : 0));
     w.nfwd = o; o = align256(o + 8);
+    // whole generations in one launch, on the table of option rows (fixed
+    // state) or of every feasible configuration
+    GAConst c = ga_shape(p);
+    c.fixed = (a->flags & MF_FIXED_STATE) ? 1 : 0;
+    c.obj.kind = a->objective.kind;
+    const uint64_t evals = (uint64_t)sp * (uint64_t)(a->gens + 1);
+    w.table = !c.fixed && ga_table_supported(c) && p->space * (uint64_t)a->n_scen * 8u <= kGaTableMaxBytes &&
+              p->space <= kGaTablePerGen * (uint64_t)a->gens && p->space <= evals;
+    w.run = (c.fixed || w.table) && ga_run_supported(c, a->pop, a->tourn_k);
+    w.table = w.table && w.run;
+    const size_t per_gen = (size_t)a->n_scen * (a->pop / 2) * ga_record_bytes(a->tourn_k, p->N);
+    if (w.run && a->gens > 0) {
+        w.span = (int)std::min<size_t>((size_t)a->gens, std::max<size_t>(kGaDrawsBytes / per_gen, 1));
+        const int n_spans = (a->gens + w.span - 1) / w.span;
+        w.span = (a->gens + n_spans - 1) / n_spans;   // equal spans
+    }
+    w.recs = o; o = align256(o + (w.run ? per_gen * w.span : 0));
+    w.lt = o; o = align256(o + (w.run && c.fixed ? (size_t)p->sumK * 16 : 0));
+    w.use_memo = !w.run && ga_memo_supported(ga_shape(p), a->n_scen, a->pop) && memo_bytes <= kGaMemoMaxBytes;
+    w.memo = o; o = align256(o + (w.use_memo ? p->space * (size_t)p->N * 16 : 0));
+    w.table_at = o; o = align256(o + (w.table ? p->space * (size_t)a->n_scen * 8 : 0));
+    w.tag = o; o = align256(o + (w.use_memo ? p->space * 4 : 0));
     w.total = o;
     return w;
 }
@@ -2304,18 +2334,63 @@ mf_status mf_ga_run(mf_problem *p, const mf_ga_args *args, void *d_ws, size_t ws
     // an empty feasible list is handled on the device (the best stays unset,
     // the final population reads all ones): no synchronisation mid-run
     MF_HIP(launch_ga_feasible(c, cnt, blk_off, n_fl, fl, s));
-    MF_HIP(launch_ga_init(args->seed, S, P, fl, n_fl, pa, bJ, bI, s));
     // generation 0 always runs the surrogates (and fills the memo); without
-    // the memo every generation does
+    // the memo every generation does (a fixed state's individuals all count;
+    // the table of configurations sets its own count)
     const unsigned long long sp = (unsigned long long)S * (unsigned long long)P;
-    MF_HIP(launch_ga_memo_clear(c.memo_tag, c.memo ? p->space : 0, c.n_forwards,
-                                c.memo ? sp : sp * (unsigned long long)(args->gens + 1), s));
-    for (int g = 0; g <= args->gens; g++) {
-        // generation g's entries carry tag g + 1
-        MF_HIP(launch_ga_fitness(c, S, P, pa, args->d_sla, args->d_omega, fit, s, (uint32_t)g + 1u));
-        MF_HIP(launch_ga_ops(c, args->seed, S, P, g, args->gens, args->tourn_k, args->p_cx, args->p_swap,
-                             args->p_mut, fl, n_fl, pa, fit, pb, bJ, bI, d_final_pop, s));
-        std::swap(pa, pb);
+    MF_HIP(launch_ga_memo_clear(c.memo_tag, w.use_memo ? p->space : 0, c.n_forwards,
+                                w.use_memo ? sp : sp * (unsigned long long)(args->gens + 1), s));
+    if (w.run) {
+        uint8_t *recs = reinterpret_cast<uint8_t *>(ws + w.recs);
+        GARunArgs r{};
+        r.c = c;
+        r.S = S;
+        r.P = P;
+        r.tk = args->tourn_k;
+        r.gens = args->gens;
+        r.seed = args->seed;
+        r.recs = recs;
+        r.sla = args->d_sla;
+        r.omega = args->d_omega;
+        r.fl = fl;
+        r.n_fl = n_fl;
+        r.pop = pa;
+        r.best_J = bJ;
+        r.best_idx = bI;
+        r.final_pop = d_final_pop;
+        if (c.fixed) {
+            FixedTableArgs ta{};
+            ta.f = fixed_base(p, args->objective, 1);
+            ta.f.sla = args->d_sla;
+            ta.f.omega = args->d_omega;
+            ta.n_steps = 1;
+            ta.lat_thr = reinterpret_cast<double2 *>(ws + w.lt);
+            for (int k = 0; k < p->A; k++) ta.state[k] = args->state[k];
+            MF_HIP(launch_fixed_table(ta, s));
+            r.lat_thr = ta.lat_thr;
+        } else {
+            double *table = reinterpret_cast<double *>(ws + w.table_at);
+            MF_HIP(launch_ga_table(c, S, args->d_sla, args->d_omega, fl, n_fl, table, s));
+            r.fit_table = table;
+        }
+        for (int g = 0; g < args->gens || g == 0; g += std::max(w.span, 1)) {
+            r.g0 = g;
+            r.g1 = std::min(g + w.span, args->gens);
+            r.init = g == 0;
+            if (r.g1 > r.g0)
+                MF_HIP(launch_ga_draws(c, args->seed, S, P, args->tourn_k, args->p_cx, args->p_swap, args->p_mut, g,
+                                       r.g1 - r.g0, fl, n_fl, recs, s));
+            MF_HIP(launch_ga_run(r, s));
+        }
+    } else {
+        MF_HIP(launch_ga_init(args->seed, S, P, fl, n_fl, pa, bJ, bI, s));
+        for (int g = 0; g <= args->gens; g++) {
+            // generation g's entries carry tag g + 1
+            MF_HIP(launch_ga_fitness(c, S, P, pa, args->d_sla, args->d_omega, fit, s, (uint32_t)g + 1u));
+            MF_HIP(launch_ga_ops(c, args->seed, S, P, g, args->gens, args->tourn_k, args->p_cx, args->p_swap,
+                                 args->p_mut, fl, n_fl, pa, fit, pb, bJ, bI, d_final_pop, s));
+            std::swap(pa, pb);
+        }
     }
     MF_HIP(hipMemcpyAsync(h_best_J, bJ, (size_t)S * 8, hipMemcpyDeviceToHost, s));
     MF_HIP(hipMemcpyAsync(h_best_idx, bI, (size_t)S * 8, hipMemcpyDeviceToHost, s));

@@ -85,6 +85,8 @@ __global__ void __launch_bounds__(NT) fixed_table_kernel(const FixedTableArgs ta
     }
     const double lat = __shfl(y, 0), thr = __shfl(y, 1);
     if (tid == 0) {
+        if (ta.lat_thr && t == 0) ta.lat_thr[r] = make_double2(lat, thr);
+        if (!a.rows) return;
         FixedRow row;
         FixedPen pp = {0.0, 0.0};
         uint32_t fl = lat <= (double)a.sla[(int64_t)t * a.n_models + i] ? 0u : kRowBad;

@@ -7,6 +7,9 @@
 // operators, 64 parent pairs per workgroup: elitism (slot 0), tournaments of
 // k draws with replacement, uniform crossover, per-gene mutation, repair of
 // VRAM-infeasible children from the feasible list.
+// Runs whose fitness comes from a table take whole generations in one launch
+// instead (mf_ga_run.hip); the kernels here serve the others, and fill the
+// table of configurations.
 //
 // Random draws: Philox4x64-10 (Salmon et al., SC'11), key (seed, 0), counter
 // (item, generation, scenario, purpose), one 64-bit word per draw;
@@ -15,74 +18,11 @@
 // mutation / repair, slot for initialisation):
 //   INIT 1 (gen 0), SEL 2 + m/4 (draw m of 2k), CX 8, SWAP 9 + i/4 (gene i),
 //   MUT 16 + w/4 (word w = 2i: mutate?, 2i+1: new value), REP 32.
-#include "mf_canon.h"
+#include "mf_ga_device.h"
 
 namespace mfi {
 
-enum { kPInit = 1, kPSel = 2, kPCx = 8, kPSwap = 9, kPMut = 16, kPRep = 32 };
-
-struct Philox4 {
-    uint64_t w[4];
-};
-
-// The 128-bit product a b: its high and low 64 bits from four 32 x 32 -> 64
-// multiply-adds (no partial sum overflows 64 bits).
-__device__ __forceinline__ void mulhilo64(uint64_t a, uint64_t b, uint64_t &hi, uint64_t &lo)
-{
-    const uint64_t a0 = (uint32_t)a, a1 = a >> 32, b0 = (uint32_t)b, b1 = b >> 32;
-    const uint64_t p00 = a0 * b0;
-    const uint64_t t1 = a0 * b1 + (p00 >> 32);
-    const uint64_t t2 = a1 * b0 + (t1 & 0xFFFFFFFFull);
-    hi = a1 * b1 + (t1 >> 32) + (t2 >> 32);
-    lo = (t2 << 32) | (p00 & 0xFFFFFFFFull);
-}
-
-__device__ __forceinline__ Philox4 philox4x64_10(uint64_t c0, uint64_t c1, uint64_t c2, uint64_t c3, uint64_t k0,
-                                                 uint64_t k1)
-{
-    const uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
-    const uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
-#pragma unroll
-    for (int r = 0; r < 10; r++) {
-        if (r) { k0 += W0; k1 += W1; }
-        uint64_t h0, l0, h1, l1;
-        mulhilo64(M0, c0, h0, l0);
-        mulhilo64(M1, c2, h1, l1);
-        const uint64_t y0 = h1 ^ c1 ^ k0, y2 = h0 ^ c3 ^ k1;
-        c0 = y0; c1 = l1; c2 = y2; c3 = l0;
-    }
-    return Philox4{{c0, c1, c2, c3}};
-}
-
-__device__ __forceinline__ uint64_t ga_draw(uint64_t seed, uint64_t item, uint64_t gen, uint64_t scen,
-                                            uint64_t purpose, int word)
-{
-    const Philox4 p = philox4x64_10(item, gen, scen, purpose, seed, 0);
-    return p.w[word & 3];
-}
-__device__ __forceinline__ double ga_uni(uint64_t r) { return (double)(r >> 11) * 0x1p-53; }
-__device__ __forceinline__ uint64_t ga_below(uint64_t r, uint64_t n) { return ((r >> 32) * n) >> 32; }
-
 // ---------------------------------------------------------------- feasible list
-
-// Mixed-radix digits of a joint index, model 0 most significant (the decode of
-// Eq. 1's configuration vector); 32-bit divisions when the space fits 32 bits.
-__device__ __forceinline__ void ga_digits(const GAConst &c, uint64_t idx, int32_t *d)
-{
-    if (c.space <= 0x100000000ull) {
-        uint32_t x = (uint32_t)idx;
-        for (int i = c.N - 1; i >= 0; i--) {
-            const uint32_t k = (uint32_t)c.K[i], q = x / k;
-            d[i] = (int32_t)(x - q * k);
-            x = q;
-        }
-    } else {
-        for (int i = c.N - 1; i >= 0; i--) {
-            d[i] = (int32_t)(idx % (uint64_t)c.K[i]);
-            idx /= (uint64_t)c.K[i];
-        }
-    }
-}
 
 __device__ __forceinline__ bool vram_feasible(const GAConst &c, uint64_t idx)
 {
@@ -272,15 +212,25 @@ __global__ void __launch_bounds__(256) ga_fitness_kernel(const GAConst c, int S,
 // each option row's aggregate columns.  The workgroup's waves take the
 // models together (a barrier per model), so that the model's weights, read
 // through scalar loads, stay in the scalar cache.
-template <int A, int H1, int H2, bool BF16>
+// TABLE: the configurations are the feasible list; each one's predictions are
+// scored for every scenario into table [S][space], for the run kernel.
+template <int A, int H1, int H2, bool BF16, bool TABLE = false>
 __global__ void __launch_bounds__(kGaFitThreads) ga_fitness_pre_kernel(const GAConst c, int S, int P,
                                                                        const uint64_t *pop, const float *sla,
                                                                        const float *omega, double *fit,
-                                                                       uint32_t memo_gen)
+                                                                       uint32_t memo_gen, const uint32_t *fl,
+                                                                       const unsigned long long *n_fl, double *table)
 {
+    if (TABLE) {
+        const unsigned long long nf = *n_fl;   // uniform: whole workgroups past the list leave at once
+        if (blockIdx.x == 0 && threadIdx.x == 0) *c.n_forwards = nf;
+        if ((uint64_t)blockIdx.x * blockDim.x >= nf) return;
+    }
     extern __shared__ __align__(16) double pre_s[];
     constexpr int PS = H1 + 2;
     float *agg_s = reinterpret_cast<float *>(pre_s + (size_t)c.sumK * PS);
+    // TABLE: [N][threads][4] terms behind the tables
+    double *terms = pre_s + (size_t)c.sumK * PS + ((size_t)c.sumK * A + 1) / 2;
     __shared__ float s_tau[kMaxN];
     __shared__ int32_t s_prev[kMaxN];
     const int tid = threadIdx.x;
@@ -299,17 +249,17 @@ __global__ void __launch_bounds__(kGaFitThreads) ga_fitness_pre_kernel(const GAC
         agg_s[t] = c.features[(int64_t)r * c.L + c.agg_cols[t - r * A]];
     }
     __syncthreads();
-    const int64_t n = (int64_t)S * P;
+    const int64_t n = TABLE ? (int64_t)*n_fl : (int64_t)S * P;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + tid;
     // lanes past the population leave: a wave that has ended no longer
     // counts at the barriers below (and one that is partly done still
     // executes them)
     if (t >= n) return;
     const int64_t tt = t;
-    const int s = (int)(tt / P);
+    const int s = TABLE ? 0 : (int)(tt / P);
     const int N = c.N, L = c.L, NIN = L + A;
     int32_t d[kMaxN];
-    const uint64_t idx = pop[tt];
+    const uint64_t idx = TABLE ? (uint64_t)fl[tt] : pop[tt];
     ga_digits(c, idx, d);
     // aggregate slots: fp32 sums in model order; the surrogates see them, or
     // the observed state held fixed (the VRAM cap still sees the candidate)
@@ -377,6 +327,24 @@ __global__ void __launch_bounds__(kGaFitThreads) ga_fitness_pre_kernel(const GAC
             y0 = canon_sigmoid(y0);
             y1 = canon_sigmoid(y1);
         }
+        if (TABLE) {
+            // the model's terms as every scenario takes them: lat, then J =
+            // (fma(omega, q, J) - P) - pen (+0 where a penalty does not apply)
+            double q = y1, Pr = 0.0, pen = 0.0;
+            if (c.obj.kind != 0) {
+                bool do_P, do_pen;
+                if (!canon_eq3(c.obj, c.opt_off[i] + d[i], y1, s_tau[i], s_prev[i], q, Pr, do_P, pen, do_pen))
+                    sla_ok = false;
+                Pr = do_P ? Pr : 0.0;
+                pen = do_pen ? pen : 0.0;
+            }
+            double *tm = terms + ((size_t)i * kGaFitThreads + tid) * 4;
+            tm[0] = y0;
+            tm[1] = q;
+            tm[2] = Pr;
+            tm[3] = pen;
+            continue;
+        }
         if (memo_gen) {   // into the run's memo (equal values where two lanes share an index)
             c.memo[(idx * (uint64_t)N + (uint64_t)i) * 2u] = y0;
             c.memo[(idx * (uint64_t)N + (uint64_t)i) * 2u + 1u] = y1;
@@ -396,29 +364,24 @@ __global__ void __launch_bounds__(kGaFitThreads) ga_fitness_pre_kernel(const GAC
             J = fma(om, y1, J);
         }
     }
+    if constexpr (TABLE) {
+        // every listed configuration meets the VRAM cap.  The models eight at
+        // a time in registers, the scenarios in the inner loop
+        for (int s2 = 0; s2 < S; s2++) {
+            double J2 = 0.0;
+            bool ok = sla_ok;
+#pragma unroll 8
+            for (int i = 0; i < N; i++) {
+                const double *tm = terms + ((size_t)i * kGaFitThreads + tid) * 4;
+                ok = ok && tm[0] <= (double)sla[(int64_t)s2 * N + i];
+                J2 = (fma((double)omega[(int64_t)s2 * N + i], tm[1], J2) - tm[2]) - tm[3];
+            }
+            table[(int64_t)s2 * (int64_t)c.space + (int64_t)idx] = ok ? J2 : -INFINITY;
+        }
+        return;
+    }
     fit[t] = (vram_ok && sla_ok) ? J : -INFINITY;
     if (memo_gen) c.memo_tag[idx] = 2u * memo_gen + (vram_ok ? 1u : 0u);
-}
-
-// One model's term of the canonical fitness, in the order every fitness
-// kernel takes it: the service constraint (Eq. 4), then J = fma(omega, thr,
-// J) or, under Eq. 3, the utility's terms (throughput floor as a constraint).
-__device__ __forceinline__ void ga_term(const GAConst &c, int s, int i, int64_t row, double lat, double thr,
-                                        const float *sla, const float *omega, const float *tau,
-                                        const int32_t *prev, double &J, bool &ok)
-{
-    if (!(lat <= (double)sla[(int64_t)s * c.N + i])) ok = false;
-    const double om = (double)omega[(int64_t)s * c.N + i];
-    if (c.obj.kind != 0) {
-        double q, Pr, pen;
-        bool do_P, do_pen;
-        if (!canon_eq3(c.obj, row, thr, tau[i], prev[i], q, Pr, do_P, pen, do_pen)) ok = false;
-        J = fma(om, q, J);
-        if (do_P) J = J - Pr;
-        if (do_pen) J = J - pen;
-    } else {
-        J = fma(om, thr, J);
-    }
 }
 
 // Generations after the first (large populations): the canonical fitness
@@ -632,29 +595,9 @@ __global__ void __launch_bounds__(64 * kGaWideWaves) ga_fitness_wide_kernel(cons
     }
 }
 
-__device__ __forceinline__ bool ga_better(double fa, uint64_t ia, double fb, uint64_t ib)
-{
-    return fa > fb || (fa == fb && ia < ib);
-}
-
 constexpr int kOpThreads = 256;                   // threads per operator workgroup
 constexpr int kOpTeam = 4;                        // lanes per parent pair
 constexpr int kOpPairs = kOpThreads / kOpTeam;    // parent pairs per operator workgroup
-
-// The Philox blocks of a parent pair kept in LDS, in a fixed order: the
-// selection blocks (2k draws), the crossover block, the swap blocks (one
-// word per gene), the mutation blocks of child 1 + 2q and of child 2 + 2q
-// (two words per gene).  A child's repair block is drawn where it is needed.
-struct OpBlocks {
-    int nsel, nswap, nmut, total;
-    __host__ __device__ OpBlocks(int tk, int N)
-        : nsel((2 * tk + 3) / 4), nswap((N + 3) / 4), nmut((N + 1) / 2), total(nsel + 1 + nswap + 2 * nmut)
-    {
-    }
-    __host__ __device__ int cx() const { return nsel; }
-    __host__ __device__ int swap() const { return nsel + 1; }
-    __host__ __device__ int mut(int t) const { return nsel + 1 + nswap + t * nmut; }
-};
 
 // Dynamic LDS of the operator kernel: the pairs' Philox words, the parents'
 // genes.
@@ -861,7 +804,20 @@ static hipError_t launch_fit_pre_t(const GAConst &c, int S, int P, const uint64_
     auto fn = c.bf16 ? ga_fitness_pre_kernel<A, H1, H2, true> : ga_fitness_pre_kernel<A, H1, H2, false>;
     const hipError_t e = ensure_dyn_lds((const void *)fn, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kGaFitThreads), lds, st, c, S, P, pop, sla, omega, fit, memo_gen);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(kGaFitThreads), lds, st, c, S, P, pop, sla, omega, fit, memo_gen, nullptr,
+                       nullptr, nullptr);
+    return hipGetLastError();
+}
+
+template <int A, int H1, int H2>
+static hipError_t launch_table_t(const GAConst &c, int S, const float *sla, const float *omega, const uint32_t *fl,
+                                 const unsigned long long *n_fl, double *table, size_t lds, hipStream_t st)
+{
+    auto fn = c.bf16 ? ga_fitness_pre_kernel<A, H1, H2, true, true> : ga_fitness_pre_kernel<A, H1, H2, false, true>;
+    const hipError_t e = ensure_dyn_lds((const void *)fn, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(fn, dim3((unsigned)((c.space + kGaFitThreads - 1) / kGaFitThreads)), dim3(kGaFitThreads), lds, st,
+                       c, S, 1, nullptr, sla, omega, nullptr, 0u, fl, n_fl, table);
     return hipGetLastError();
 }
 
@@ -873,6 +829,26 @@ static size_t ga_pre_lds(const GAConst &c)
 static bool ga_pre_shape(int A, int H1, int H2)
 {
     return (A == 2 || A == 4 || A == 6 || A == 8) && ((H1 == 32 && H2 == 32) || (H1 == 64 && (H2 == 32 || H2 == 64)));
+}
+
+static size_t ga_table_lds(const GAConst &c) { return ((ga_pre_lds(c) + 15) & ~(size_t)15) + (size_t)c.N * kGaFitThreads * 32; }
+
+bool ga_table_supported(const GAConst &c)
+{
+    return c.pre && ga_pre_lds(c) <= kGaPreLdsBytes && ga_table_lds(c) <= 163840 - 1024 && ga_pre_shape(c.A, c.H1, c.H2);
+}
+
+hipError_t launch_ga_table(const GAConst &c, int S, const float *sla, const float *omega, const uint32_t *fl,
+                           const unsigned long long *n_fl, double *table, hipStream_t st)
+{
+    const size_t lds = ga_table_lds(c);
+#define MF_GA_TAB(AA, HA, HB) \
+    if (c.A == AA && c.H1 == HA && c.H2 == HB) return launch_table_t<AA, HA, HB>(c, S, sla, omega, fl, n_fl, table, lds, st);
+    MF_GA_TAB(2, 32, 32) MF_GA_TAB(4, 32, 32) MF_GA_TAB(6, 32, 32) MF_GA_TAB(8, 32, 32)
+    MF_GA_TAB(2, 64, 32) MF_GA_TAB(4, 64, 32) MF_GA_TAB(6, 64, 32) MF_GA_TAB(8, 64, 32)
+    MF_GA_TAB(2, 64, 64) MF_GA_TAB(4, 64, 64) MF_GA_TAB(6, 64, 64) MF_GA_TAB(8, 64, 64)
+#undef MF_GA_TAB
+    return hipErrorInvalidValue;
 }
 
 bool ga_memo_supported(const GAConst &c, int S, int P)

@@ -427,6 +427,7 @@ struct FixedTableArgs {
     FixedArgs f;
     int n_steps;
     uint32_t *ticket;
+    double2 *lat_thr;           // optional [sumK]: the canonical predictions of step 0 (f.rows may then be null)
     float state[MF_MAX_STEPS * MF_MAX_AGG];
 };
 
@@ -483,6 +484,27 @@ struct GAConst {
     double *memo;
     uint32_t *memo_tag;
     unsigned long long *n_forwards;   // individuals whose fitness ran the surrogates (with the memo)
+};
+
+// Generations [g0, g1] of every scenario in one launch (mf_ga_run.hip): the
+// populations of g0 (drawn here when init, else read from pop) go through the
+// operators up to generation g1, whose elite updates the best; g1 == gens
+// writes the final population, otherwise generation g1's goes to pop for the
+// next launch.
+struct GARunArgs {
+    GAConst c;
+    int S, P, tk, g0, g1, gens, init;
+    uint64_t seed;
+    const uint8_t *recs;              // draws of generations g0 .. g1 - 1: [g1 - g0][S][words][P / 2]
+    const double2 *lat_thr;           // [sumK] canonical predictions per option row (fixed state), or
+    const double *fit_table;          // [S][space] the fitness of every VRAM-feasible configuration
+    const float *sla, *omega;         // [S][N]
+    const uint32_t *fl;
+    const unsigned long long *n_fl;
+    uint64_t *pop;                    // [S][P]
+    double *best_J;
+    uint64_t *best_idx;
+    uint64_t *final_pop;              // optional
 };
 
 // Raise a kernel's dynamic-LDS limit to at least `bytes` on the current
@@ -546,6 +568,7 @@ constexpr size_t kGaStageBytes = 64 * 1024;   // ... copying the weights to LDS 
 constexpr int kGaFitThreads = 512;             // large populations: lanes (individuals) per fitness workgroup
 constexpr int kGaMemoThreads = 256;            // ... after the first generation: individuals per memo workgroup
 constexpr uint64_t kGaMemoMaxBytes = 256ull << 20;   // the run's memo of predictions, at most this large
+constexpr uint64_t kGaTableMaxBytes = 1024ull << 20;  // the table of configurations' fitness, at most this large
 constexpr size_t kGaPreLdsBytes = 96 * 1024;   // ... continuing the local-feature chains staged in this much LDS
 constexpr int64_t kGaWideStagedWgs = 512;    // ... and then running this many workgroups at most
 int ga_fitness_supported(int nin, int h1, int h2);
@@ -560,6 +583,16 @@ hipError_t launch_ga_fitness(const GAConst &c, int S, int P, const uint64_t *pop
 bool ga_memo_supported(const GAConst &c, int S, int P);
 hipError_t launch_ga_memo_clear(uint32_t *tag, uint64_t n, unsigned long long *n_forwards,
                                 unsigned long long first, hipStream_t st);
+constexpr size_t kGaDrawsBytes = 64u << 20;    // records of a span of generations, at most this large
+int ga_record_bytes(int tk, int N);
+bool ga_run_supported(const GAConst &c, int P, int tk);
+bool ga_table_supported(const GAConst &c);
+hipError_t launch_ga_table(const GAConst &c, int S, const float *sla, const float *omega, const uint32_t *fl,
+                           const unsigned long long *n_fl, double *table, hipStream_t st);
+hipError_t launch_ga_draws(const GAConst &c, uint64_t seed, int S, int P, int tk, float p_cx, float p_swap, float p_mut,
+                           int gen0, int gens, const uint32_t *fl, const unsigned long long *n_fl, uint8_t *recs,
+                           hipStream_t st);
+hipError_t launch_ga_run(const GARunArgs &r, hipStream_t st);
 hipError_t launch_ga_ops(const GAConst &c, uint64_t seed, int S, int P, int gen, int gens, int tk, float p_cx,
                          float p_swap, float p_mut, const uint32_t *fl, const unsigned long long *n_fl,
                          const uint64_t *pop, const double *fit, uint64_t *next, double *best_J,

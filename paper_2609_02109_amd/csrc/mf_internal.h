@@ -188,6 +188,11 @@ struct FastArgs {
     const float *features;      // [sumK][n_local]
     const int32_t *agg_cols;    // [A] (original slot order)
     int n_local, vram_slot;
+    // > 0: configuration t of the range is column t / spread of tile t %
+    // spread (spread = the number of tiles): neighbours, which share most
+    // options and so rank together, go to different workgroups.  The range
+    // lies below 2^32.  0: tile t / 32.
+    uint32_t spread;
 };
 
 // ---------------------------------------------------------------------------
@@ -522,6 +527,10 @@ hipError_t launch_precompute_p(const float *features, const float *weights, cons
                                int n_rows, int L, int A, int H, int64_t wstride,
                                const int32_t *row_model, float *image_p, int pst, const Pow2Scales &sc,
                                hipStream_t s);
+hipError_t launch_fast_n8_h32(const FastArgs &a, const FastConst &fc, int grid, int kp, int mode, hipStream_t s);
+hipError_t launch_fast_n8_h64(const FastArgs &a, const FastConst &fc, int grid, int kp, int mode, hipStream_t s);
+hipError_t launch_fast_n16_h32(const FastArgs &a, const FastConst &fc, int grid, int kp, int mode, hipStream_t s);
+hipError_t launch_fast_n16_h64(const FastArgs &a, const FastConst &fc, int grid, int kp, int mode, hipStream_t s);
 hipError_t launch_fast_impl(const FastArgs &a, const FastConst &fc, int grid, int kp, int mode, hipStream_t s);
 int fast_waves_for(int n_models, const FastLayout &lay, int kp, int act);
 int fast_kernel_supported(int n_models, int A, int H, int kp);
@@ -546,6 +555,7 @@ hipError_t launch_select(const SelectArgs &a, hipStream_t s);
 hipError_t launch_gather_small(const GatherArgs &g, hipStream_t s);
 hipError_t launch_finish_small(const FinishArgs &f, const FastConst &fc, hipStream_t s);
 size_t fast_small_epilogue_bytes(int n_models);
+constexpr int kCertChunk = 64;                 // entries certified per chunk (small ranges)
 constexpr uint64_t kSmallRange = 1ull << 20;   // fp32 ranges up to this size finish in one workgroup
 size_t fixed_lds_bytes(int sumK, bool eq3);
 size_t static_lds_bytes(int n_steps, int sumK, int n_models, bool eq3);

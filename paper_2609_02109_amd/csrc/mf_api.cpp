@@ -546,7 +546,7 @@ int choose_kp(int top_k, int max_kp)
     return kp;
 }
 
-void stride_digits(const mf_problem &p, uint64_t stride, uint32_t *out)
+void mixed_digits(const mf_problem &p, uint64_t stride, uint32_t *out)
 {
     const uint64_t s = stride % p.space;
     uint64_t x = s;
@@ -766,9 +766,7 @@ mf_status run_range(mf_problem *p, const mf_search_args *args, uint64_t lo, uint
     fa.lay = p->lay;
     fa.lo = lo;
     fa.n = n;
-    fa.total_waves = w.grid * w.waves;
     fa.waves = w.waves;
-    stride_digits(*p, (uint64_t)fa.total_waves * 32u, fa.stride_digits);
     fa.sla = args->d_sla;
     fa.omega = args->d_omega;
     fa.res = R;
@@ -823,6 +821,8 @@ mf_status run_range(mf_problem *p, const mf_search_args *args, uint64_t lo, uint
         // the search and writes every field of the result block; the fast
         // kernel's time comes from the workgroups' wall-clock stamps
         fa.small = 1;
+        fa.total_waves = w.grid * w.waves;
+        mixed_digits(*p, (uint64_t)fa.total_waves * 32u, fa.digits);
         fa.ep_bytes = (int)ep_bytes;
         fa.canon = p->d_canon;
         fa.seg_cap = w.seg_cap;
@@ -883,6 +883,7 @@ mf_status run_range(mf_problem *p, const mf_search_args *args, uint64_t lo, uint
         fa.spread = 0;
     } else {
         MF_HIP2(hipMemsetAsync(R, 0, sizeof(DevResult), s));
+        mixed_digits(*p, lo, fa.digits);
         if (ev0) MF_HIP2(hipEventRecord(ev0, s));
         MF_HIP2(launch_fast_path(p, fa, w.grid, w.kp, kModeSearch, s));
         if (ev1) MF_HIP2(hipEventRecord(ev1, s));
@@ -910,6 +911,7 @@ mf_status run_range(mf_problem *p, const mf_search_args *args, uint64_t lo, uint
         fa.theta = h.theta;
         fa.mask = nullptr;
         fa.pred = nullptr;
+        mixed_digits(*p, lo, fa.digits);
         MF_HIP2(hipMemsetAsync(&R->n_collect, 0, sizeof(unsigned long long), s));
         if (ev0) MF_HIP2(hipEventRecord(ev0, s));
         MF_HIP2(launch_fast_path(p, fa, w.grid, w.kp, kModeCollect, s));
@@ -2173,11 +2175,9 @@ mf_status mf_eval_fast(mf_problem *p, const uint64_t *d_idx, int64_t n, float *d
     fa.lo = 0;
     fa.n = (uint64_t)n;
     fa.idx_list = d_idx;
-    const uint64_t tiles = ((uint64_t)n + 31) / 32;
-    fa.waves = fast_waves_for(p->N, p->lay, 16, p->act);
-    const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>((tiles + fa.waves - 1) / fa.waves,
+    const uint64_t per_wg = (uint64_t)kSearchWaves * 64;
+    const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>(((uint64_t)n + per_wg - 1) / per_wg,
                                                                     (uint64_t)p->num_cus));
-    fa.total_waves = grid * fa.waves;
     fa.sla = p->d_zeros;
     fa.omega = p->d_zeros;
     fa.pred = d_pred;

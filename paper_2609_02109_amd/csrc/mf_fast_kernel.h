@@ -1,9 +1,9 @@
 // Fast path of the exhaustive surrogate search (fp32 MFMA), gfx950.
 //
-// One wave evaluates a tile of 32 consecutive joint indices per step:
-//   decode       mixed-radix digits (Eq. 1) by odometer: the wave decodes its
-//                first tile once and then adds a fixed stride in mixed radix;
-//                each lane adds its column (0..31) with carries
+// One wave evaluates tiles of 32 joint indices, one per step in a small range
+// (small_kernel), two in a large one (scan_kernel):
+//   decode       mixed-radix digits (Eq. 1): by reciprocals from the offset, or,
+//                in a small range with a dump, by odometer
 //   aggregate    fp32 sum in model order of every model's option row
 //                (the aggregate field of Section III-B), from LDS; slot 0 is
 //                the VRAM sum, compared with the cap (Eq. 4)
@@ -338,37 +338,19 @@ __device__ inline void small_certify(const FastArgs &args, const FastConst &fc, 
     }
 }
 
+// Per-model parameters of a search after the image in LDS:
+// [0,16) sla_lo  [16,32) sla_hi  [32,48) omega  [48,64) first option row per model (int)
+// [64,80) floor tau  [80,96) previous variant (int)  [96,112) throughput bound
+// [112,128) option count per model (int)  [128,144) latency bound  [144,160) aggregate column (int)
 // OBJ: score with the full utility of Eq. 3 (otherwise the linear objective).
 // SIG: the surrogates' outputs pass a sigmoid; the latency decision then
 // compares the pre-activation with logit thresholds.
-// SMALL: small ranges (kModeSearch): certification follows in the same launch;
-// a kernel of its own, so that this tail's registers do not count against the
-// scan of large ranges.
-template <int MAXN, int A, int H, int WAVES, bool OBJ, bool SIG, bool SMALL>
-__global__ void __launch_bounds__(WAVES * 64, 1)
-fast_kernel(const FastArgs args, const FastConst fc, const int mode_arg, const int kp)
+template <bool OBJ, bool SIG>
+__device__ __forceinline__ void fast_params(const FastArgs &args, const FastConst &fc, float *par)
 {
-    const int mode = SMALL ? (int)kModeSearch : mode_arg;
-    const uint32_t spread = SMALL ? args.spread : 0u;
-    constexpr int MB = H / 32;         // 32-row blocks of a hidden layer
-    static_assert(A <= 8, "layer 1 takes at most 4 aggregate slots per lane half");
-    constexpr bool L1ONE = A <= 4;     // two slots per lane half: one layer-1 instruction per block
-    constexpr int AP = 8;              // aggregate row stride in LDS: [half][4]
-    extern __shared__ float4 smem4[];
-    float *smem = reinterpret_cast<float *>(smem4);
-    const FastLayout &Ly = args.lay;
     const int N = fc.n_models;
-    __shared__ unsigned int s_nwork;   // small ranges: certification entries of the workgroup
-    __shared__ double s_inv[MAXN];     // 1 / K (spread ranges)
-
-    for (int t = threadIdx.x; t < args.image_f4; t += blockDim.x) smem4[t] = args.image[t];
-    // [0,16) sla_lo  [16,32) sla_hi  [32,48) omega  [48,64) first option row per model (int)
-    // [64,80) floor tau  [80,96) previous variant (int)  [96,112) throughput bound
-    // [112,128) option count per model (int)  [128,144) latency bound  [144,160) aggregate column (int)
-    float *par = smem + Ly.total_floats;
     int *par_off = reinterpret_cast<int *>(par + 48);
     int *par_prev = reinterpret_cast<int *>(par + 80);
-    unsigned long long *lst = reinterpret_cast<unsigned long long *>(smem + args.lst_off);
 #pragma unroll
     for (int i = 0; i < kMaxN; i++) {
         // compile-time index into the argument block (keeps it out of scratch)
@@ -393,7 +375,6 @@ fast_kernel(const FastArgs args, const FastConst fc, const int mode_arg, const i
             }
             par[32 + i] = args.omega[i];
             par_off[i] = fc.opt_off[i];
-            if (i < MAXN) s_inv[i] = 1.0 / (double)fc.K[i];
             reinterpret_cast<int *>(par + 112)[i] = fc.K[i];
             par[128 + i] = args.sla[i];
             if constexpr (OBJ) {
@@ -403,7 +384,489 @@ fast_kernel(const FastArgs args, const FastConst fc, const int mode_arg, const i
             }
         }
     }
-    if (SMALL && threadIdx.x < (unsigned)Ly.A)
+}
+
+// After the scan: the workgroup's counts and its merged candidate list (the
+// merge kernel, or the finish of a small range, takes them on).
+template <int WAVES>
+__device__ __forceinline__ void write_wg_result(WaveList<1> &wl, uint32_t c_vram, uint32_t c_feas,
+                                                unsigned long long *lst, const FastArgs &args, int kp, int lane, int wv)
+{
+    __shared__ unsigned long long s_cnt[2 * WAVES];
+    const unsigned long long sv = wave_sum64(c_vram), sf = wave_sum64(c_feas);
+    if (lane == 0) {
+        s_cnt[wv] = sv;
+        s_cnt[WAVES + wv] = sf;
+    }
+    if (args.lst_off == 0) __syncthreads();   // the lists overwrite the weights: every wave's scan is done
+    if (lane < kp) lst[wv * kp + lane] = wl.s[0];
+    wl_tree_merge<1, WAVES>(wl, lst, kp, wv, lane, kp);
+    if (wv == 0) {
+        if (lane < kp) args.wg_lists[(uint64_t)blockIdx.x * kp + lane] = wl.s[0];
+        if (lane < 2) {
+            unsigned long long t = 0;
+            for (int w = 0; w < WAVES; w++) t += s_cnt[lane * WAVES + w];
+            args.wg_counts[2 * (uint64_t)blockIdx.x + lane] = t;
+        }
+    }
+}
+
+// One 32-configuration tile's state in the scan of large ranges.
+template <int MB>
+struct ScanTile {
+    uint32_t xh[MB * 8], xl[MB * 8];   // h1 as binary16 pairs: x1, x2 of registers 2 p, 2 p + 1
+    floatx16 h1[MB];                   // layer-1 accumulators
+    floatx16 acc;                      // layer 2, one output block
+    float pl, pt;                      // layer-3 partial sums (lat, thr)
+};
+
+// The lane's 16 accumulator rows of a 32-row block, in accumulator order.
+__device__ __forceinline__ floatx16 scan_load16(const float *p)
+{
+    floatx16 v;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const float4 f = *reinterpret_cast<const float4 *>(p + 8 * q);
+        v[4 * q + 0] = f.x;
+        v[4 * q + 1] = f.y;
+        v[4 * q + 2] = f.z;
+        v[4 * q + 3] = f.w;
+    }
+    return v;
+}
+
+// relu and binary16 pieces of the pair p of h1.
+template <int MB>
+__device__ __forceinline__ void scan_split(ScanTile<MB> &t, int p)
+{
+    const int mb = p >> 3, r = 2 * (p & 7);
+    t.xl[p] = split_f16_pair(relu_f32(t.h1[mb][r]), relu_f32(t.h1[mb][r + 1]), &t.xh[p]);
+}
+
+__device__ __forceinline__ f16x8 pairs_f16x8(const uint32_t *v)
+{
+    f16x8 r;
+    __builtin_memcpy(&r, v, 16);
+    return r;
+}
+
+// Row r of the tile's layer-2 block into the layer-3 sums.
+template <int MB>
+__device__ __forceinline__ void scan_l3(ScanTile<MB> &t, const floatx16 &acc, int r, const float4 (&wl)[4],
+                                        const float4 (&wt)[4])
+{
+    const float h = relu_f32(acc[r]);
+    const float4 a = wl[r >> 2], b = wt[r >> 2];
+    const int j = r & 3;
+    t.pl = fmaf(j == 0 ? a.x : j == 1 ? a.y : j == 2 ? a.z : a.w, h, t.pl);
+    t.pt = fmaf(j == 0 ? b.x : j == 1 ? b.y : j == 2 ? b.z : b.w, h, t.pt);
+}
+
+// Large ranges, the collect pass and lists: two tiles of 32 configurations per
+// wave, 8 waves per workgroup (2 per SIMD, up to 256 registers).  What bounds
+// it is the vector and matrix issue of a SIMD: per (tile, model) at H = 64 28
+// matrix instructions (17.4 ns each, 490 ns) and about 215 vector ones (2 ns
+// each beside the matrix cores, whatever their kind).  A tile's vector work
+// (the split of h1, layer 3) lies between the other tile's matrix
+// instructions, the operands both tiles share (W1, W2, b2, W3) are read from
+// LDS once, and a lane decides one configuration: lane l of a step holds
+// configuration l, tile l / 32 column l % 32 (decode, tail and lists once per
+// 64 configurations).  One tile per wave and 4 waves per SIMD took 872 ns per
+// (tile, model); two tiles in a fixed order of steps 790; steps taken from a
+// counter and the decode without branches 720.
+template <int MAXN, int A, int H, bool OBJ, bool SIG>
+__global__ void __launch_bounds__(kSearchWaves * 64, 1)
+scan_kernel(const FastArgs args, const FastConst fc, const int mode, const int kp)
+{
+    constexpr int MB = H / 32, WAVES = kSearchWaves, NW = (MAXN + 3) / 4;
+    static_assert(A <= 8, "layer 1 takes at most 4 aggregate slots per lane half");
+    constexpr bool L1ONE = A <= 4;     // two slots per lane half: one layer-1 instruction per block
+    constexpr int AP = 8;              // aggregate row stride in LDS: [half][4]
+    extern __shared__ float4 smem4[];
+    float *smem = reinterpret_cast<float *>(smem4);
+    const FastLayout &Ly = args.lay;
+    const int N = fc.n_models;
+    for (int t = threadIdx.x; t < args.image_f4; t += blockDim.x) smem4[t] = args.image[t];
+    float *par = smem + Ly.total_floats;
+    const int *par_off = reinterpret_cast<const int *>(par + 48), *par_prev = reinterpret_cast<const int *>(par + 80);
+    unsigned long long *lst = reinterpret_cast<unsigned long long *>(smem + args.lst_off);
+    fast_params<OBJ, SIG>(args, fc, par);
+    // decode constants per model: 1 / K; K and the first index's digit (the
+    // unused models decode to digit 0 and add a row of zeros)
+    __shared__ double s_inv[MAXN];
+    __shared__ uint2 s_kd[MAXN];
+    __shared__ alignas(16) float s_zero[AP];
+    __shared__ unsigned int s_next;   // the workgroup's steps handed out
+#pragma unroll
+    for (int i = 0; i < MAXN; i++)
+        if (threadIdx.x == (unsigned)i) {   // a compile-time index keeps the argument block out of scratch
+            s_inv[i] = i < N ? 1.0 / (double)fc.K[i] : 1.0;
+            s_kd[i] = i < N ? uint2{(uint32_t)fc.K[i], args.digits[i]} : uint2{1u, 0u};
+        }
+    if (threadIdx.x < AP) s_zero[threadIdx.x] = 0.f;
+    if (threadIdx.x == 0) s_next = WAVES;
+    // global bound on |fast J - canonical J|: keys and certification entries
+    // carry the upper bound U = J + eJ
+    const double eJ = bound_eJ(fc, args.omega);
+    if (mode == kModeSearch && blockIdx.x == 0 && threadIdx.x == 0) args.res->eJ = eJ;
+    __syncthreads();
+
+    const int lane = threadIdx.x & 63, half = lane >> 5;
+    const float4 *cen_p = reinterpret_cast<const float4 *>(smem + Ly.off_c + 4 * half);
+    const float sx_s[4] = {half ? fc.agg_scale[1][0] : fc.agg_scale[0][0], half ? fc.agg_scale[1][1] : fc.agg_scale[0][1],
+                           half ? fc.agg_scale[1][2] : fc.agg_scale[0][2], half ? fc.agg_scale[1][3] : fc.agg_scale[0][3]};
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wave-uniform
+    const uint64_t n = args.n;
+    const uint64_t n_steps = (n + 63) >> 6;
+
+    WaveList<1> wl;
+    wl_init(wl);
+    uint32_t c_vram = 0, c_feas = 0;
+    WorkBuf wbuf;   // certification entries
+    wbuf.e = 0ull;
+    wbuf.j = 0.f;
+    wbuf.n = 0;
+
+    // The workgroup's steps are blockIdx.x, + gridDim.x, ...; its waves take
+    // them one by one: of the two waves of a SIMD one is served first and runs
+    // a third faster (12.4 us a step against 17 at six models).  With equal
+    // shares the slower one set the time (29.1 ms against 26.6).
+    uint64_t step = (uint64_t)wv * gridDim.x + blockIdx.x;
+    while (step < n_steps) {
+        unsigned int taken = 0;
+        if (lane == 0) taken = atomicAdd(&s_next, 1u);
+        const uint64_t off = step * 64u + (uint64_t)lane;
+        const bool valid = off < n;
+        // digits of the lane's configuration, 8 bits each, four to a word
+        uint32_t dg[NW] = {};
+        if (mode == kModeList) {
+            uint64_t x = args.idx_list[valid ? off : n - 1];
+#pragma unroll
+            for (int j = MAXN - 1; j >= 0; j--)
+                if (j < N) {
+                    const uint64_t k = (uint64_t)fc.K[j];
+                    dg[j / 4] |= (uint32_t)(x % k) << (8 * (j % 4));
+                    x /= k;
+                }
+        } else {
+            // offset (below 2^32) by reciprocals, the half added keeping the
+            // product clear of the integers; then the first index's digits
+            uint32_t x = valid ? (uint32_t)off : 0u, carry = 0;
+#pragma unroll
+            for (int j = MAXN - 1; j >= 0; j--) {
+                const uint2 kd = s_kd[j];
+                const uint32_t q = (uint32_t)(((double)x + 0.5) * s_inv[j]);
+                const uint32_t t = x - q * kd.x + kd.y + carry;
+                x = q;
+                carry = t >= kd.x ? 1u : 0u;
+                dg[j / 4] |= (t - (carry ? kd.x : 0u)) << (8 * (j % 4));
+            }
+        }
+        // both tiles' digits in every lane: column l % 32 of tile t
+        uint32_t dt[2][NW];
+#pragma unroll
+        for (int w = 0; w < NW; w++) {
+            const auto r = __builtin_amdgcn_permlane32_swap(dg[w], dg[w], false, false);
+            dt[0][w] = r[0];
+            dt[1][w] = r[1];
+        }
+
+        // aggregate field (model order, fp32).  Lane half h accumulates the
+        // slots it feeds to layer 1 as B operand: internal slots 2s + h.
+        // Slot 0 (half 0, s 0) is the VRAM sum.
+        float ah[2][4] = {};
+#pragma unroll
+        for (int j = 0; j < MAXN; j++) {
+            const float *g = (j < N ? smem + Ly.off_g + fc.opt_off[j] * AP : s_zero) + 4 * half;
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+                const float4 v = *reinterpret_cast<const float4 *>(g + ((dt[t][j / 4] >> (8 * (j % 4))) & 0xFFu) * AP);
+                ah[t][0] += v.x;
+                ah[t][1] += v.y;
+                ah[t][2] += v.z;
+                ah[t][3] += v.w;
+            }
+        }
+        bool vram_ok;
+        {
+            // the lane's own sum: both lower halves hold slot 0
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(ah[0][0]), __float_as_uint(ah[1][0]), false,
+                                                            false);
+            vram_ok = __uint_as_float(r[0]) <= fc.vram_cap;
+        }
+        // layer 1's B operands, shared by every model of the step: the lane's
+        // slots s (2s + half) as x = 2^ex (a - c) in binary16 pieces x1 + x2.
+        // Four slots (A > 4): in k = 8 half + j, j and j + 4 both hold slot
+        // j, bx1 its x1, bx2 its x2.  Two slots: one operand, j = 0, 1 and
+        // 2, 3 hold x1 of slots 0, 1, j = 4, 5 and 6, 7 their x2.
+        f16x8 bx1[2], bx2[2];
+        {
+            const float4 cen = cen_p[0];
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+                uint32_t q[2], r[2];
+                r[0] = split_f16_pair((ah[t][0] - cen.x) * sx_s[0], (ah[t][1] - cen.y) * sx_s[1], &q[0]);
+                if constexpr (L1ONE) {
+                    const uint32_t w1[4] = {q[0], q[0], r[0], r[0]};
+                    __builtin_memcpy(&bx1[t], w1, 16);
+                    bx2[t] = bx1[t];
+                } else {
+                    r[1] = split_f16_pair((ah[t][2] - cen.z) * sx_s[2], (ah[t][3] - cen.w) * sx_s[3], &q[1]);
+                    const uint32_t w1[4] = {q[0], q[1], q[0], q[1]}, w2[4] = {r[0], r[1], r[0], r[1]};
+                    __builtin_memcpy(&bx1[t], w1, 16);
+                    __builtin_memcpy(&bx2[t], w2, 16);
+                }
+            }
+        }
+
+        float J = 0.f, EJ = 0.f, MJ = 0.f;   // fast J; under Eq. 3 its bound and magnitude
+        bool anyfail = false;
+        uint32_t umask = 0;   // models whose service decision is left to the canonical pass
+        // Loads run ahead of their use, held in place by scheduling barriers: a
+        // register pair of W2 operands is reloaded for the next output block
+        // (or the next model's first) as soon as its last instruction is
+        // issued, layer-3 weights likewise, the next model's layer-1 rows
+        // beside the last block.  Left to itself the compiler sinks them to
+        // their use, and the LDS latency showed at every block.
+        ScanTile<MB> T[2];
+        f16x8 a1[MB], wa[2 * MB], wb[2 * MB];
+        floatx16 bias;
+        const auto load_rows = [&](int i) {
+            const int sh = 8 * (i & 3), base = par_off[i];
+            uint32_t w0 = dt[0][0], w1 = dt[1][0];
+#pragma unroll
+            for (int w = 1; w < NW; w++)
+                if (i >= 4 * w) {
+                    w0 = dt[0][w];
+                    w1 = dt[1][w];
+                }
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+                const uint32_t row = (uint32_t)base + (((t ? w1 : w0) >> sh) & 0xFFu);
+                const float *prow = smem + Ly.off_p + row * (uint32_t)Ly.PST + 4 * half;
+#pragma unroll
+                for (int mb = 0; mb < MB; mb++)
+                    T[t].h1[mb] = scan_load16(prow + 32 * mb);
+            }
+            // W1_agg 2^(e1 - ex) in binary16 pieces w1 + w2, row 32 mb + l%32
+            // of lane l.  Four slots: 16 bytes per lane and block, w1 (j < 4)
+            // then w2 (j >= 4) of the slots 2 (j % 4) + l/32; one A operand
+            // for both instructions, w1 x1 + w2 x1, then w1 x2 + w2 x2.  Two
+            // slots: 8 bytes, w1 then w2 of slots l/32 and 2 + l/32, read
+            // twice into one operand, all four products in one instruction.
+#pragma unroll
+            for (int mb = 0; mb < MB; mb++) {
+                if constexpr (L1ONE) {
+                    const uint2 p = (reinterpret_cast<const uint2 *>(smem + Ly.off_w1a + i * (MB * 64 * 2)) + lane)[mb * 64];
+                    a1[mb] = as_f16x8(uint4{p.x, p.y, p.x, p.y});
+                } else {
+                    a1[mb] = as_f16x8((reinterpret_cast<const uint4 *>(smem + Ly.off_w1a + i * (MB * 64 * 4)) + lane)[mb * 64]);
+                }
+            }
+        };
+        load_rows(0);
+        {
+            const uint4 *w2p = reinterpret_cast<const uint4 *>(smem + Ly.off_w2) + lane;
+#pragma unroll
+            for (int kb = 0; kb < 2 * MB; kb++) {
+                wa[kb] = as_f16x8(w2p[(kb * 2 + 0) * 64]);
+                wb[kb] = as_f16x8(w2p[(kb * 2 + 1) * 64]);
+            }
+            bias = scan_load16(smem + Ly.off_b2 + 4 * half);
+        }
+        for (int i = 0; i < N; i++) {
+            const int nx = i + 1 < N ? i + 1 : i;
+            const uint4 *w2p = reinterpret_cast<const uint4 *>(smem + Ly.off_w2 + i * (H * H)) + lane;
+            const uint4 *w2n = reinterpret_cast<const uint4 *>(smem + Ly.off_w2 + nx * (H * H)) + lane;
+            const float *w3 = smem + Ly.off_w3 + i * (2 * H) + 4 * half;
+            // the tail's values
+            const float2 b3 = *reinterpret_cast<const float2 *>(smem + Ly.off_b3 + 4 * i);
+            const float p_lo = par[i], p_hi = par[16 + i], p_om = par[32 + i];
+            float4 vr0, vr1;
+            if constexpr (OBJ) {
+                uint32_t w = dg[0];
+#pragma unroll
+                for (int q = 1; q < NW; q++) w = i >= 4 * q ? dg[q] : w;
+                const uint32_t row = (uint32_t)par_off[i] + ((w >> (8 * (i & 3))) & 0xFFu);
+                vr0 = args.obj.vrow[2 * row];
+                vr1 = args.obj.vrow[2 * row + 1];
+            }
+            // ---- layer 1: P[row] + W1_agg a
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+                T[t].pl = 0.f;
+                T[t].pt = 0.f;
+#pragma unroll
+                for (int mb = 0; mb < MB; mb++) {
+                    T[t].h1[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1[mb], bx1[t], T[t].h1[mb], 0, 0, 0);
+                    if constexpr (!L1ONE)
+                        T[t].h1[mb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1[mb], bx2[t], T[t].h1[mb], 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // layer-3 weights of the block whose sums are due
+            float4 w3l[4], w3t[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                w3l[q] = *reinterpret_cast<const float4 *>(w3 + (0 * MB * 4 + q) * 8);
+                w3t[q] = *reinterpret_cast<const float4 *>(w3 + (1 * MB * 4 + q) * 8);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int p = 0; p < 8 * MB; p++) scan_split(T[0], p);
+            __builtin_amdgcn_sched_barrier(0);
+            // ---- layer 2: b2 + W2 h1, one output block at a time.  h1 (the
+            // relu'd layer-1 accumulators) as binary16 pieces, x1 = x
+            // truncated, x2 = (x - x1) rounded to nearest.  W2 as two binary16
+            // pieces (w1 + w2 ~ 2^e2 W2) in the A-operand order of
+            // v_mfma_f32_32x32x16_f16: per (mb2, mb1, kh) 1 KB of w1 then 1 KB
+            // of w2, lane l's 16 bytes holding K-block elements 0..7.  The
+            // small cross products first, while the accumulator holds only the
+            // bias (each matrix instruction's error grows with the accumulator
+            // it adds to), then the leading ones.
+            constexpr int NM = 6 * MB;          // matrix instructions per tile and block
+#pragma unroll
+            for (int mb2 = 0; mb2 < MB; mb2++) {
+#pragma unroll
+                for (int t = 0; t < 2; t++) {
+                    floatx16 acc = bias;
+                    const floatx16 prev = T[1 - t].acc;
+#pragma unroll
+                    for (int m = 0; m < NM; m++) {
+                        const int kb = m < 4 * MB ? m >> 1 : m - 4 * MB;
+                        const bool lo2 = m < 4 * MB && (m & 1);         // w1 x2
+                        const bool hi2 = m < 4 * MB && !(m & 1);        // w2 x1
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(hi2 ? wb[kb] : wa[kb],
+                                                                     pairs_f16x8((lo2 ? T[t].xl : T[t].xh) + 4 * kb),
+                                                                     acc, 0, 0, 0);
+                        // the other tile's vector work beside it
+                        if (t == 0 && mb2 == 0) {
+#pragma unroll
+                            for (int p = m * 8 * MB / NM; p < (m + 1) * 8 * MB / NM; p++) scan_split(T[1], p);
+                        } else {
+#pragma unroll
+                            for (int r = m * 16 / NM; r < (m + 1) * 16 / NM; r++) {
+                                scan_l3(T[1 - t], prev, r, w3l, w3t);
+                                if (t == 0 && (r & 3) == 3) {   // tile 1 was the last to need these
+                                    const int q = r >> 2;
+                                    w3l[q] = *reinterpret_cast<const float4 *>(w3 + ((0 * MB + mb2) * 4 + q) * 8);
+                                    w3t[q] = *reinterpret_cast<const float4 *>(w3 + ((1 * MB + mb2) * 4 + q) * 8);
+                                }
+                            }
+                        }
+                        if (t == 1) {
+                            const bool last = mb2 + 1 == MB;
+                            const uint4 *src = last ? w2n : w2p + (mb2 + 1) * MB * 4 * 64;
+                            if (hi2) wb[kb] = as_f16x8(src[(kb * 2 + 1) * 64]);
+                            if (m >= 4 * MB) wa[kb] = as_f16x8(src[(kb * 2 + 0) * 64]);
+                            if (m == 1)
+                                bias = scan_load16(last ? smem + Ly.off_b2 + nx * H + 4 * half
+                                                        : smem + Ly.off_b2 + i * H + 4 * half + 32 * (mb2 + 1));
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    T[t].acc = acc;
+                }
+            }
+            load_rows(nx);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < 16; r++) scan_l3(T[1], T[1].acc, r, w3l, w3t);
+            // each half's sums join: tile 0's in lanes 0..31, tile 1's above
+            const auto sl = __builtin_amdgcn_permlane32_swap(__float_as_uint(T[0].pl), __float_as_uint(T[1].pl), false, false);
+            const auto st = __builtin_amdgcn_permlane32_swap(__float_as_uint(T[0].pt), __float_as_uint(T[1].pt), false, false);
+            const float lat = (__uint_as_float(sl[0]) + __uint_as_float(sl[1])) + b3.x;
+            const float pre = (__uint_as_float(st[0]) + __uint_as_float(st[1])) + b3.y;
+            const float thr = SIG ? sigmoid_f32(pre) : pre;
+            bool pass = lat <= p_lo, fail = lat > p_hi;
+            if constexpr (OBJ) {
+                const Eq3Term t = eq3_term(vr0, vr1, thr, par[96 + i], p_om, par[64 + i], par_prev[i], args.obj.alpha,
+                                           args.obj.beta, args.obj.delta);
+                fail = fail || t.fail;
+                pass = pass && t.pass;
+                J += t.c;
+                EJ += t.e;
+                MJ += t.mag;
+            } else {
+                J = fmaf(p_om, thr, J);
+            }
+            anyfail |= fail;
+            umask |= (pass || fail) ? 0u : (1u << i);
+            if (args.pred && valid) {
+                args.pred[(off * (uint64_t)N + (uint64_t)i) * 2u + 0u] = SIG ? sigmoid_f32(lat) : lat;
+                args.pred[(off * (uint64_t)N + (uint64_t)i) * 2u + 1u] = thr;
+            }
+        }
+
+        if (mode != kModeList) {
+            const bool anyunc = umask != 0u;
+            const bool sla_sure = !anyfail && !anyunc;
+            const bool feas_sure = valid && vram_ok && sla_sure;
+            // a latency decision the bound cannot settle: re-evaluated
+            // canonically when it can change the count (VRAM ok) or, in dump
+            // mode, the mask
+            const bool unc = valid && !anyfail && anyunc && (vram_ok || args.mask != nullptr);
+            // Eq. 3: the sum of per-model bounds, plus the fp32 sum over models
+            // (N u relative to the magnitudes)
+            const float U = OBJ ? f32_up((double)J + (double)EJ * (1.0 + 0x1p-10) + (double)MJ * N * 0x1p-22 + 1e-30)
+                                : f32_up((double)J + eJ);
+            if (mode == kModeSearch) {
+                c_vram += (valid && vram_ok) ? 1u : 0u;
+                c_feas += feas_sure ? 1u : 0u;
+                const unsigned long long went = (unsigned long long)(uint32_t)off | ((unsigned long long)umask << 32);
+                wb_append(wbuf, unc, went, U, lane, &args.res->n_work, args.work, args.work_J, args.work_cap);
+                const unsigned long long key = feas_sure
+                    ? (((unsigned long long)ord_f32(U) << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)off))
+                    : 0ull;
+                wl_offer_many(wl, key, lane, kp);
+                if (args.mask && valid)
+                    args.mask[off] = (uint8_t)((vram_ok ? 1u : 0u) | (sla_sure ? 2u : 0u) |
+                                               (feas_sure ? 4u : 0u) | (unc ? 8u : 0u));
+            } else {
+                list_append(feas_sure && (double)U >= args.theta, (uint32_t)off, lane, &args.res->n_collect,
+                            args.collect, args.collect_cap);
+            }
+        }
+        step = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)taken) * gridDim.x + blockIdx.x;
+    }
+
+    if (mode == kModeSearch) {
+        wb_flush(wbuf, lane, &args.res->n_work, args.work, args.work_J, args.work_cap);
+        write_wg_result<WAVES>(wl, c_vram, c_feas, lst, args, kp, lane, wv);
+    }
+}
+
+// Small ranges: a tile of 32 configurations per wave (latency counts here, so
+// the range goes to as many waves as there are tiles), then the certification.
+template <int MAXN, int A, int H, int WAVES, bool OBJ, bool SIG>
+__global__ void __launch_bounds__(WAVES * 64, 1)
+small_kernel(const FastArgs args, const FastConst fc, const int kp)
+{
+    const uint32_t spread = args.spread;
+    constexpr int MB = H / 32;         // 32-row blocks of a hidden layer
+    static_assert(A <= 8, "layer 1 takes at most 4 aggregate slots per lane half");
+    constexpr bool L1ONE = A <= 4;     // two slots per lane half: one layer-1 instruction per block
+    constexpr int AP = 8;              // aggregate row stride in LDS: [half][4]
+    extern __shared__ float4 smem4[];
+    float *smem = reinterpret_cast<float *>(smem4);
+    const FastLayout &Ly = args.lay;
+    const int N = fc.n_models;
+    __shared__ unsigned int s_nwork;   // small ranges: certification entries of the workgroup
+    __shared__ double s_inv[MAXN];     // 1 / K (spread ranges)
+
+    for (int t = threadIdx.x; t < args.image_f4; t += blockDim.x) smem4[t] = args.image[t];
+    float *par = smem + Ly.total_floats;
+    int *par_off = reinterpret_cast<int *>(par + 48);
+    int *par_prev = reinterpret_cast<int *>(par + 80);
+    unsigned long long *lst = reinterpret_cast<unsigned long long *>(smem + args.lst_off);
+    fast_params<OBJ, SIG>(args, fc, par);
+    {
+        // (a compile-time index keeps the argument block out of scratch)
+#pragma unroll
+        for (int i = 0; i < MAXN; i++)
+            if (threadIdx.x == (unsigned)i && i < N) s_inv[i] = 1.0 / (double)fc.K[i];
+    }
+    if (threadIdx.x < (unsigned)Ly.A)
         reinterpret_cast<int *>(par + 144)[threadIdx.x] = args.agg_cols[threadIdx.x];
     constexpr bool eq3 = OBJ;
     // global bound on |fast J - canonical J|: keys and certification entries
@@ -415,7 +878,6 @@ fast_kernel(const FastArgs args, const FastConst fc, const int mode_arg, const i
         s_nwork = 0;
         t_start = (unsigned long long)wall_clock64();
     }
-    if (mode == kModeSearch && !SMALL && blockIdx.x == 0 && threadIdx.x == 0) args.res->eJ = eJ;
     __syncthreads();
 
     const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
@@ -431,7 +893,7 @@ fast_kernel(const FastArgs args, const FastConst fc, const int mode_arg, const i
     const uint64_t n_tiles = (n + 31) >> 5;
 
     uint32_t bd[MAXN] = {};
-    if (mode != kModeList && spread == 0u) {
+    if (spread == 0u) {
         uint64_t x = args.lo + (uint64_t)gw * 32u;
 #pragma unroll
         for (int j = MAXN - 1; j >= 0; j--) {
@@ -448,10 +910,6 @@ fast_kernel(const FastArgs args, const FastConst fc, const int mode_arg, const i
     WaveList<1> wl;
     wl_init(wl);
     uint32_t c_vram = 0, c_feas = 0;
-    WorkBuf wbuf;   // certification entries (the general search path)
-    wbuf.e = 0ull;
-    wbuf.j = 0.f;
-    wbuf.n = 0;
 
     for (uint64_t tile = gw; tile < n_tiles; tile += (uint64_t)args.total_waves) {
         const uint64_t off = spread ? (uint64_t)((uint32_t)col * spread + (uint32_t)tile)
@@ -469,18 +927,6 @@ fast_kernel(const FastArgs args, const FastConst fc, const int mode_arg, const i
                     const uint32_t q = (uint32_t)(((double)x + 0.5) * s_inv[j]);
                     d[j] = x - q * (uint32_t)fc.K[j];
                     x = q;
-                }
-            }
-        } else if (mode == kModeList) {
-            uint64_t x = args.idx_list[valid ? off : n - 1];
-#pragma unroll
-            for (int j = MAXN - 1; j >= 0; j--) {
-                if (j < N) {
-                    const uint64_t k = (uint64_t)fc.K[j];
-                    d[j] = (uint32_t)(x % k);
-                    x /= k;
-                } else {
-                    d[j] = 0;
                 }
             }
         } else {
@@ -674,59 +1120,48 @@ fast_kernel(const FastArgs args, const FastConst fc, const int mode_arg, const i
             }
         }
 
-        if (mode != kModeList) {
-            const bool mine = valid && half == 0;
-            const bool anyunc = umask != 0u;
-            const bool sla_sure = !anyfail && !anyunc;
-            const bool feas_sure = mine && vram_ok && sla_sure;
-            // a latency decision the bound cannot settle: re-evaluated
-            // canonically when it can change the count (VRAM ok) or, in dump
-            // mode, the mask
-            const bool unc = mine && !anyfail && anyunc && (vram_ok || args.mask != nullptr);
-            // Eq. 3: the sum of per-model bounds, plus the fp32 sum over models
-            // (N u relative to the magnitudes)
-            const float U = eq3 ? f32_up((double)J + (double)EJ * (1.0 + 0x1p-10) + (double)MJ * N * 0x1p-22 + 1e-30)
-                                : f32_up((double)J + eJ);
-            if (mode == kModeSearch) {
-                c_vram += (mine && vram_ok) ? 1u : 0u;
-                c_feas += feas_sure ? 1u : 0u;
-                const unsigned long long went = (unsigned long long)(uint32_t)off | ((unsigned long long)umask << 32);
-                if constexpr (SMALL) {
-                    const unsigned long long m = __ballot(unc);
-                    if (m) {
-                        unsigned int base = 0;
-                        if (lane == 0) base = atomicAdd(&s_nwork, (unsigned int)__popcll(m));
-                        base = (unsigned int)__builtin_amdgcn_readfirstlane((int)base);
-                        const unsigned int slot = base + (unsigned int)__popcll(m & ((1ull << lane) - 1ull));
-                        if (unc && slot < args.seg_cap) {
-                            const uint64_t at = (uint64_t)blockIdx.x * args.seg_cap + slot;
-                            args.seg[at] = went;
-                            args.seg_J[at] = U;
-                        }
-                    }
-                } else {
-                    wb_append(wbuf, unc, went, U, lane, &args.res->n_work, args.work, args.work_J, args.work_cap);
-                }
-                const unsigned long long key = feas_sure
-                    ? (((unsigned long long)ord_f32(U) << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)off))
-                    : 0ull;
-                wl_offer_many(wl, key, lane, kp);
-                if (args.mask && mine)
-                    args.mask[off] = (uint8_t)((vram_ok ? 1u : 0u) | (sla_sure ? 2u : 0u) |
-                                               (feas_sure ? 4u : 0u) | (unc ? 8u : 0u));
-            } else {
-                list_append(feas_sure && (double)U >= args.theta, (uint32_t)off, lane, &args.res->n_collect,
-                            args.collect, args.collect_cap);
+        const bool mine = valid && half == 0;
+        const bool anyunc = umask != 0u;
+        const bool sla_sure = !anyfail && !anyunc;
+        const bool feas_sure = mine && vram_ok && sla_sure;
+        // a latency decision the bound cannot settle: re-evaluated
+        // canonically when it can change the count (VRAM ok) or, in dump
+        // mode, the mask
+        const bool unc = mine && !anyfail && anyunc && (vram_ok || args.mask != nullptr);
+        // Eq. 3: the sum of per-model bounds, plus the fp32 sum over models
+        // (N u relative to the magnitudes)
+        const float U = eq3 ? f32_up((double)J + (double)EJ * (1.0 + 0x1p-10) + (double)MJ * N * 0x1p-22 + 1e-30)
+                            : f32_up((double)J + eJ);
+        c_vram += (mine && vram_ok) ? 1u : 0u;
+        c_feas += feas_sure ? 1u : 0u;
+        const unsigned long long went = (unsigned long long)(uint32_t)off | ((unsigned long long)umask << 32);
+        const unsigned long long m = __ballot(unc);
+        if (m) {
+            unsigned int base = 0;
+            if (lane == 0) base = atomicAdd(&s_nwork, (unsigned int)__popcll(m));
+            base = (unsigned int)__builtin_amdgcn_readfirstlane((int)base);
+            const unsigned int slot = base + (unsigned int)__popcll(m & ((1ull << lane) - 1ull));
+            if (unc && slot < args.seg_cap) {
+                const uint64_t at = (uint64_t)blockIdx.x * args.seg_cap + slot;
+                args.seg[at] = went;
+                args.seg_J[at] = U;
             }
         }
+        const unsigned long long key = feas_sure
+            ? (((unsigned long long)ord_f32(U) << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)off))
+            : 0ull;
+        wl_offer_many(wl, key, lane, kp);
+        if (args.mask && mine)
+            args.mask[off] = (uint8_t)((vram_ok ? 1u : 0u) | (sla_sure ? 2u : 0u) | (feas_sure ? 4u : 0u) |
+                                       (unc ? 8u : 0u));
 
-        if (mode != kModeList && spread == 0u) {
+        if (spread == 0u) {
             // advance the tile base by the grid stride, in mixed radix
             uint32_t carry = 0;
 #pragma unroll
             for (int j = MAXN - 1; j >= 0; j--) {
                 if (j < N) {
-                    uint32_t t = bd[j] + args.stride_digits[j] + carry;
+                    uint32_t t = bd[j] + args.digits[j] + carry;
                     carry = t >= (uint32_t)fc.K[j] ? 1u : 0u;
                     bd[j] = carry ? t - (uint32_t)fc.K[j] : t;
                 }
@@ -734,69 +1169,54 @@ fast_kernel(const FastArgs args, const FastConst fc, const int mode_arg, const i
         }
     }
 
-    if (mode == kModeSearch && !SMALL)
-        wb_flush(wbuf, lane, &args.res->n_work, args.work, args.work_J, args.work_cap);
-    if (mode == kModeSearch) {
-        // counts and list per workgroup (the merge kernel sums and merges them)
-        __shared__ unsigned long long s_cnt[2 * WAVES];
-        const unsigned long long sv = wave_sum64(c_vram), sf = wave_sum64(c_feas);
-        if (lane == 0) {
-            s_cnt[wv] = sv;
-            s_cnt[WAVES + wv] = sf;
-        }
-        if (args.lst_off == 0) __syncthreads();   // the lists overwrite the weights: every wave's scan is done
-        if (lane < kp) lst[wv * kp + lane] = wl.s[0];
-        wl_tree_merge<1, WAVES>(wl, lst, kp, wv, lane, kp);
-        if (wv == 0) {
-            if (lane < kp) args.wg_lists[(uint64_t)blockIdx.x * kp + lane] = wl.s[0];
-            if (lane < 2) {
-                unsigned long long t = 0;
-                for (int w = 0; w < WAVES; w++) t += s_cnt[lane * WAVES + w];
-                args.wg_counts[2 * (uint64_t)blockIdx.x + lane] = t;
-            }
-        }
-        if constexpr (SMALL) {
-            // s_nwork is final: every wave's appends precede the tree merge's barriers
-            small_certify<H, WAVES, OBJ, SIG>(args, fc, smem, par, wl.s[0], kp, s_nwork, lane, wv, t_start);
-        }
-    }
+    write_wg_result<WAVES>(wl, c_vram, c_feas, lst, args, kp, lane, wv);
+    // s_nwork is final: every wave's appends precede the tree merge's barriers
+    small_certify<H, WAVES, OBJ, SIG>(args, fc, smem, par, wl.s[0], kp, s_nwork, lane, wv, t_start);
 }
 
-template <int MAXN, int A, int H, int WAVES>
-static hipError_t launch_fast_t(const FastArgs &a, const FastConst &fc, int grid, int kp, int mode,
-                                hipStream_t s)
+// The small kernel has 16 waves per workgroup where its registers and LDS allow
+// (a.waves), the scan always 8.
+template <int MAXN, int A, int H, bool SIG>
+static hipError_t launch_fast_t(const FastArgs &a, const FastConst &fc, int grid, int kp, int mode, hipStream_t s)
 {
     FastArgs b = a;
-    b.lst_off = fast_lists_in_image(a.lay, WAVES, kp) ? 0 : a.lay.total_floats + kFastPar;
-    const size_t lds = fast_dyn_lds(a.lay, WAVES, kp, (size_t)a.ep_bytes);
-    const bool small = b.small && mode == kModeSearch, eq3 = a.obj.kind != 0;
-    auto fn = eq3 ? (small ? fast_kernel<MAXN, A, H, WAVES, true, false, true>
-                           : fast_kernel<MAXN, A, H, WAVES, true, false, false>)
-                  : (small ? fast_kernel<MAXN, A, H, WAVES, false, false, true>
-                           : fast_kernel<MAXN, A, H, WAVES, false, false, false>);
-    if constexpr (MAXN == kMaxN && WAVES == kSearchWaves)   // the sigmoid output runs on the generic kernel
-        if (fc.act) fn = eq3 ? (small ? fast_kernel<MAXN, A, H, WAVES, true, true, true>
-                                      : fast_kernel<MAXN, A, H, WAVES, true, true, false>)
-                             : (small ? fast_kernel<MAXN, A, H, WAVES, false, true, true>
-                                      : fast_kernel<MAXN, A, H, WAVES, false, true, false>);
+    const bool eq3 = a.obj.kind != 0;
+    const int waves = a.small ? a.waves : kSearchWaves;
+    b.lst_off = fast_lists_in_image(a.lay, waves, kp) ? 0 : a.lay.total_floats + kFastPar;
+    const size_t lds = fast_dyn_lds(a.lay, waves, kp, (size_t)a.ep_bytes);
+    if (a.small) {
+        if (mode != kModeSearch) return hipErrorInvalidValue;
+        auto fn = eq3 ? small_kernel<MAXN, A, H, kSearchWaves, true, SIG>
+                      : small_kernel<MAXN, A, H, kSearchWaves, false, SIG>;
+        if (waves != kSearchWaves) {
+            if constexpr (MAXN <= 8 && !SIG)
+                fn = eq3 ? small_kernel<MAXN, A, H, kSearchWavesWide, true, SIG>
+                         : small_kernel<MAXN, A, H, kSearchWavesWide, false, SIG>;
+            else
+                return hipErrorInvalidValue;
+        }
+        hipError_t e = ensure_dyn_lds((const void *)fn, lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(fn, dim3(grid), dim3(waves * 64), lds, s, b, fc, kp);
+        return hipGetLastError();
+    }
+    auto fn = eq3 ? scan_kernel<MAXN, A, H, true, SIG> : scan_kernel<MAXN, A, H, false, SIG>;
     hipError_t e = ensure_dyn_lds((const void *)fn, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(WAVES * 64), lds, s, b, fc, mode, kp);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(waves * 64), lds, s, b, fc, mode, kp);
     return hipGetLastError();
 }
 
-// The kernels of one option-count class and hidden width (a source file each,
-// so that they compile in parallel).
+// The kernels of one model-count class and hidden width (a source file each,
+// so that they compile in parallel).  Sigmoid outputs run on the 16-model
+// kernels.
 template <int MAXN, int H>
 hipError_t launch_fast_for(const FastArgs &a, const FastConst &fc, int grid, int kp, int mode, hipStream_t s)
 {
-    const bool wide = a.waves == kSearchWavesWide;
-    if (wide && (MAXN > 8 || fc.act)) return hipErrorInvalidValue;
-#define MF_FAST_CASE(AA)                                                                                     \
-    if (a.lay.A == AA) {                                                                                     \
-        if constexpr (MAXN <= 8)                                                                             \
-            if (wide) return launch_fast_t<MAXN, AA, H, kSearchWavesWide>(a, fc, grid, kp, mode, s);         \
-        return launch_fast_t<MAXN, AA, H, kSearchWaves>(a, fc, grid, kp, mode, s);                           \
+#define MF_FAST_CASE(AA)                                                                                       \
+    if (a.lay.A == AA) {                                                                                       \
+        if (!fc.act) return launch_fast_t<MAXN, AA, H, false>(a, fc, grid, kp, mode, s);                       \
+        if constexpr (MAXN == kMaxN) return launch_fast_t<MAXN, AA, H, true>(a, fc, grid, kp, mode, s);        \
     }
     MF_FAST_CASE(2) MF_FAST_CASE(4) MF_FAST_CASE(6) MF_FAST_CASE(8)
 #undef MF_FAST_CASE

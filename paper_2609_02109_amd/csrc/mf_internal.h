@@ -12,8 +12,8 @@
 namespace mfi {
 
 constexpr int kMaxN = MF_MAX_MODELS;
-constexpr int kSearchWaves = 8;          // waves per workgroup of the fast search kernel (base)
-constexpr int kSearchWavesWide = 16;     // ... when registers and LDS allow 4 waves per SIMD
+constexpr int kSearchWaves = 8;          // waves per workgroup of the fp32 scan (2 per SIMD, two tiles each)
+constexpr int kSearchWavesWide = 16;     // ... of a small range's kernel, when registers and LDS allow 4 per SIMD
 constexpr int kCertWaves = 4;            // waves per workgroup of the canonical kernels
 constexpr int kDefaultWorklist = 1 << 20; // certification list capacity (entries)
 constexpr int kFastPar = 160;            // floats of per-model parameters after the fp32 fast image in LDS
@@ -148,9 +148,9 @@ struct FastArgs {
     FastLayout lay;
     uint64_t lo, n;             // range [lo, lo+n); list mode: n entries of idx_list
     const uint64_t *idx_list;   // list mode only
-    uint32_t stride_digits[kMaxN]; // mixed-radix digits of (total waves * 32) mod |Lambda|
-    int total_waves;
-    int waves;                  // waves per workgroup (kSearchWaves or kSearchWavesWide)
+uint32_t digits[kMaxN];     // mixed-radix digits, small ranges: of total_waves * 32 mod |Lambda|; scan: of lo
+    int total_waves;            // small ranges
+    int waves;                  // small ranges: waves per workgroup (kSearchWaves or kSearchWavesWide)
     const float *sla;           // device [N]
     const float *omega;         // device [N]
     DevResult *res;

@@ -467,8 +467,7 @@ float f32_up_host(double x)
 // the bf16 kernel): cst[2 + o] fixed terms of output o (the |b3| part of the
 // fp32 layer-3 bound and the fp64 rounding of the canonical layers 2 and 3),
 // cst[4 + o] = sum_v |W3[o][v]| |b2[v]|, cst[6 + o] = max_u sum_v
-// |W3[o][v]| |W2[v][u]|, cst[8 + o] = max_v |W3[o][v]|; *mag_thr bounds |thr|
-// over the joint space.  Layer 1 is identical on both sides (the same fp32
+// |W3[o][v]| |W2[v][u]|; *mag_thr bounds |thr| over the joint space.  Layer 1 is identical on both sides (the same fp32
 // chain and bf16 rounding).  Layer 3 runs as four partial fp32 chains of H/8
 // terms per output, summed pairwise, plus the cross-half add and b3: at most
 // H/8 + 4 roundings.
@@ -527,9 +526,6 @@ void bf16_bounds(const mf_problem &p, const std::vector<float> &F, const std::ve
         cst[2 + o] = f32_up_host((g3 * std::fabs((double)b3[o]) + e64) * 1.01 + 1e-30);
         cst[4 + o] = f32_up_host(cb * (1.0 + 1e-6));
         cst[6 + o] = f32_up_host(rmax * (1.0 + 1e-6));
-        double w3max = 0.0;
-        for (int v = 0; v < H; v++) w3max = std::max(w3max, std::fabs((double)W3[o * H + v]));
-        cst[8 + o] = f32_up_host(w3max);
         if (o == 1) *mag_thr = f32_up_host(m3 * 1.01);
     }
 }

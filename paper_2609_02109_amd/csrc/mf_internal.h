@@ -203,8 +203,7 @@ uint32_t digits[kMaxN];     // mixed-radix digits, small ranges: of total_waves 
 //   b2  [H]
 //   w3  [o][mb][q][half][4]       W3[o][32 mb + 8 q + 4 half + j]
 //   cst [12]                      b3[0], b3[1], then per output (lat, thr):
-//                                 k0 (fixed bound terms), |W3||b2|, max_u (|W3||W2|)_u,
-//                                 max_v |W3[o][v]|
+//                                 k0 (fixed bound terms), |W3||b2|, max_u (|W3||W2|)_u
 // Resident in LDS for the whole launch: g [sumK][half][4] aggregate slots of
 // every option row (slot 2s + half at [half][s], original slot order) and the
 // VRAM column gv [sumK].  In global memory: phat [sumK][PST], the fp32 chain

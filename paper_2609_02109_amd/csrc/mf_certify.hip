@@ -450,7 +450,6 @@ __global__ void __launch_bounds__(kFinWaves * 64) finish_small_kernel(const Fini
     __shared__ unsigned long long s_red[8][kFinWaves];
     __shared__ K128 klst[kFinWaves * 64];
     __shared__ K128 s_floor;
-    __shared__ unsigned long long s_tot[8];
     constexpr int W = kFinWaves;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -510,32 +509,20 @@ __global__ void __launch_bounds__(kFinWaves * 64) finish_small_kernel(const Fini
         s_red[7][wv] = (rest << 32) | st;
     }
     __syncthreads();
-    // one quantity per wave: its total over the waves (lanes W .. 63 repeat)
-    for (int q = wv; q < 8; q += W) {
-        const unsigned long long x = s_red[q][lane % W];
-        const unsigned long long y = lane < W ? x : 0ull;
-        const unsigned long long t = q < 5 ? wave_sum64(y)
-                                   : q == 5 ? wave_min64(x)
-                                   : q == 6 ? wave_max64(x)
-                                            : (wave_max64(x >> 32) << 32) | wave_or64(x & 0xFFFFFFFFull);
-        if (lane == 0) s_tot[q] = t;
+    unsigned long long tnv = 0, tnf = 0, tnw = 0, tovf = 0, tnfc = 0, tt0 = ~0ull, tt1 = 0, trest = 0, tst = 0;
+    for (int w = 0; w < W; w++) {
+        tnv += s_red[0][w];
+        tnf += s_red[1][w];
+        tnw += s_red[2][w];
+        tovf += s_red[3][w];
+        tnfc += s_red[4][w];
+        tt0 = s_red[5][w] < tt0 ? s_red[5][w] : tt0;
+        tt1 = s_red[6][w] > tt1 ? s_red[6][w] : tt1;
+        const unsigned long long rs = s_red[7][w] >> 32;
+        trest = rs > trest ? rs : trest;
+        tst |= s_red[7][w] & 0xFFFFFFFFull;
     }
-
-    // ---- a lower bound of the k-th largest key: the k-th largest of up to
-    // 64 maxima of the workgroups' first (largest) keys, distinct candidates
-    if (wv == W - 1) {
-        K128 m = {0ull, 0ull};
-        for (int g = lane; g < n_wg; g += 64) {
-            const K128 x = ckeys[(uint32_t)g * (uint32_t)k];
-            if (gt128(x, m)) m = x;
-        }
-        const K128 srt = sort128_desc(m, lane);
-        const K128 fk = {readlane64(srt.hi, k - 1), readlane64(srt.lo, k - 1)};
-        if (lane == 0) s_floor = fk;
-    }
-    __syncthreads();
-    const unsigned long long tnw = s_tot[2];
-    if (s_tot[3] || tnw > f.work_cap) {
+    if (tovf || tnw > f.work_cap) {
         if (tid == 0) {
             R->status = kStatWorkOverflow;
             R->n_work = (unsigned long long)f.work_cap + 1;
@@ -548,6 +535,19 @@ __global__ void __launch_bounds__(kFinWaves * 64) finish_small_kernel(const Fini
         return;
     }
 
+    // ---- a lower bound of the k-th largest key: the k-th largest of up to
+    // 64 maxima of the workgroups' first (largest) keys, distinct candidates
+    if (wv == 0) {
+        K128 m = {0ull, 0ull};
+        for (int g = lane; g < n_wg; g += 64) {
+            const K128 x = ckeys[(uint32_t)g * (uint32_t)k];
+            if (gt128(x, m)) m = x;
+        }
+        const K128 srt = sort128_desc(m, lane);
+        const K128 fk = {readlane64(srt.hi, k - 1), readlane64(srt.lo, k - 1)};
+        if (lane == 0) s_floor = fk;
+    }
+    __syncthreads();
     const K128 floor_key = s_floor;
 
     // ---- the exact top-k: the keys at or above the bound, offered per wave,
@@ -589,10 +589,8 @@ __global__ void __launch_bounds__(kFinWaves * 64) finish_small_kernel(const Fini
             // the k-th canonical J exceeds it (or nothing is unevaluated);
             // otherwise the fallback collects every U >= C_k (every
             // sure-feasible configuration when fewer than k were found)
-            const unsigned long long trest = s_tot[7] >> 32, tt0 = s_tot[5], tt1 = s_tot[6];
-            const unsigned long long tnv = s_tot[0], tnf = s_tot[1], tnfc = s_tot[4];
             const double restU = trest ? (double)unord_f32((uint32_t)trest) : -INFINITY;
-            unsigned stat = (unsigned)s_tot[7];
+            unsigned stat = (unsigned)tst;
             double Ck = -INFINITY;
             bool verified;
             if (n_top >= k) {

@@ -214,6 +214,7 @@ class Problem:
         nb = C.c_size_t()
         _check(lib.mf_problem_bytes(C.byref(self.desc), C.byref(nb)), "mf_problem_bytes")
         self._tables = torch.empty(max(int(nb.value), 256), dtype=torch.uint8, device=self.device)
+        self._on = self._tables.device
         _keep_for(stream, feats, w, self._tables)
         h = C.c_void_p()
         _check(lib.mf_problem_create(C.byref(self.desc), _ptr(feats), _ptr(w), _ptr(self._tables),
@@ -251,6 +252,8 @@ class Problem:
         if a is None:
             return None
         if isinstance(a, torch.Tensor):
+            if a.dtype is dtype and a.device == self._on and a.is_contiguous():
+                return a
             return a.to(self.device, dtype).contiguous()
         return torch.as_tensor(np.asarray(a), dtype=dtype, device=self.device).contiguous()
 
@@ -283,8 +286,11 @@ class Problem:
         d_om = self._dev(omega, torch.float32)
         mask = pred = None
         if dump:
-            mask = torch.zeros(max(hi - lo, 1), dtype=torch.uint8, device=self.device)
-            pred = torch.zeros((max(hi - lo, 1), self.N, 2), dtype=torch.float32, device=self.device)
+            # a search on the candidates' own aggregates writes every element
+            # (the two fills took 10-15 of 95 us at 105,435 configurations)
+            new = torch.empty if state is None else torch.zeros
+            mask = new(max(hi - lo, 1), dtype=torch.uint8, device=self.device)
+            pred = new((max(hi - lo, 1), self.N, 2), dtype=torch.float32, device=self.device)
         flags = (MF_DUMP if dump else 0) | (MF_FIXED_STATE if state is not None else 0)
         args = SearchArgs(lo, hi, int(k), flags, _ptr(d_sla), _ptr(d_om),
                           _ptr(mask), _ptr(pred), objective_args(objective, self.N))

@@ -616,7 +616,7 @@ WsLayout ws_layout(const mf_problem &p, uint64_t n, int top_k, uint32_t worklist
     // 1e-5 (the fallback pass then runs).  At k = 16 over 206 workgroups 6
     // entries instead of 9: one round of canonical forwards instead of two
     // (the fast kernel 33.1 -> 27.2 us at 105,435 configurations, k = 16).
-    w.spread = w.small && p.space <= (1ull << 32);
+    w.spread = w.small && w.grid > 1 && p.space <= (1ull << 32);
     const double m = 1.5 * top_k / w.grid;
     w.eval_spread = std::min(w.kp, (int)std::ceil(m + 6.0 * std::sqrt(m) + 3.0));
     const size_t n_seg = (size_t)w.seg_cap * (w.small ? w.grid : 0);

@@ -37,7 +37,8 @@ TRAFFIC_SOURCE_SHA = "7ae62e82fdc3c035"
 
 
 # the fast kernel's source: its file and the headers it includes
-TRAFFIC_SOURCES = ("paper_2609_02109_amd/csrc/mf_search.hip", "paper_2609_02109_amd/csrc/mf_device.h",
+TRAFFIC_SOURCES = ("paper_2609_02109_amd/csrc/mf_search_n8_h64.hip", "paper_2609_02109_amd/csrc/mf_fast_kernel.h",
+                   "paper_2609_02109_amd/csrc/mf_canon.h", "paper_2609_02109_amd/csrc/mf_device.h",
                    "paper_2609_02109_amd/csrc/mf_internal.h", "include/mf.h")
 
 
@@ -201,28 +202,6 @@ def bench_n8(mf, torch, seed, steps, warmup):
             "roofline_bf16_peak": n8_bf16_roofline(inst, kms)}
 
 
-# Vector issue of the chip: one wave64 VALU instruction per clock per CU
-# (4 SIMD16 units, 4 clocks each), 256 CUs at 2.4 GHz, in G instructions/s
-PEAK_VALU_GINST = 256 * 2.4
-
-
-def fixed_inner_models(inst):
-    """Models whose digits vary inside a block of the fixed-state scan: the
-    shortest suffix with at least 256 joint options (the library's split)."""
-    m, j = 1, inst.n_models
-    while j > 0 and m < 256:
-        j -= 1
-        m *= int(inst.n_options[j])
-    return inst.n_models - j
-
-
-def fixed_alg_ops(inst):
-    # per configuration: the inner models' chain steps (fp64 FMA, fp32 VRAM
-    # add, service-flag OR each) and the three decisions (VRAM cap, service,
-    # J screen against the k-th best); the outer prefix is shared per block
-    return 3 * fixed_inner_models(inst) + 3
-
-
 def bench_fixed(mf, torch, seed, steps, warmup):
     """The searches with the observed state held fixed (Section III-B): the
     surrogates run once per option row, the joint space is scanned over the
@@ -236,18 +215,14 @@ def bench_fixed(mf, torch, seed, steps, warmup):
         st = synth.make_state(inst, seed)
         ms, kms, r = measure_search(mf, torch, inst, k, steps, warmup, objective=obj, state=st)
         n = inst.space_size
-        ops = fixed_alg_ops(inst)
-        ach = ops / 64 * n / (kms * 1e-3) / 1e9
-        log(f"fixed-state {name}: {ms:.3f} ms/step, scan kernel {kms:.3f} ms, n_feas={r.n_feas} "
+        log(f"fixed-state {name}: {ms:.3f} ms/step, kernel {kms:.3f} ms, n_feas={r.n_feas} "
             f"argmax={r.top_idx[0]}")
-        out[name] = {"ms_to_top": ms, "top_k": k, "joint_configs_per_s": n / (ms * 1e-3), "scan_kernel_ms": kms,
+        out[name] = {"ms_to_top": ms, "top_k": k, "joint_configs_per_s": n / (ms * 1e-3), "kernel_ms": kms,
                      "n_feas": int(r.n_feas), "argmax": int(r.top_idx[0]),
-                     "roofline": {"bound": "alu", "achieved": ach, "peak": PEAK_VALU_GINST,
-                                  "unit": "G VALU wave-instr/s", "frac": ach / PEAK_VALU_GINST,
-                                  "alg_lane_ops_per_config": ops,
-                                  "note": "the 9 operations include the J chain, which blocks whose exact J upper "
-                                          "bound is under the wave's k-th J skip; under Eq. 3 the chain's four "
-                                          "penalty subtractions per configuration are not counted"}}
+                     "roofline": {"bound": "latency", "kernel": "mitm_kernel", "us": kms * 1e3,
+                                  "note": "meet in the middle: every configuration is decided by counts and "
+                                          "bounds over the products of two halves, so the time does not go "
+                                          "with the number of configurations"}}
     out["workload"] = ("the N=6 and N=8 searches with the surrogates' aggregate input held at a seeded observed "
                        "state (linear objective; N=6 also with Eq. 3)")
     return out
@@ -316,9 +291,9 @@ def measure_ga(mf, torch, seed, steps, warmup):
             "evaluations_per_s": evals / (ms * 1e-3), "surrogate_forwards": fwd,
             "best_J": [float(x) for x in r["best_J"]],
             "best_idx": [int(x) for x in r["best_idx"]],
-            "roofline": {"bound": "latency", "kernel": "whole GA run (fitness, operators, feasible list)",
+            "roofline": {"bound": "latency", "kernel": "whole GA run (feasible list, table, draws, generations)",
                          "generations": gp.gens + 1, "us_per_generation": ms * 1e3 / (gp.gens + 1),
-                         "launches_per_generation": 2, "flops_per_forward": per,
+                         "flops_per_forward": per,
                          "forward_tflops": per * fwd / (ms * 1e-3) / 1e12, "traffic": None}}
 
 

@@ -495,8 +495,8 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
     // rotated by a fixed step (prefixes that share options have the best
     // bounds together: a run of neighbours, or a stride of whole digits,
     // would give one wave many of them), each lane keeps its two largest bounds and the largest it dropped, and the
-    // wave hands on its `a.list` largest (descending, then the largest of the
-    // rest): sorted lists of 128 in every wave and their merges took 70 of
+    // wave hands on the `a.list` largest of the kept ones (descending), then the
+    // largest of all the others: sorted lists of 128 in every wave and their merges took 70 of
     // 145 us at 2^20 prefixes.
     const int grid = (int)gridDim.x;
     WaveList<NS> L;
@@ -584,7 +584,7 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
 
     // ==== the last workgroup: candidates, exact values, the result
     constexpr int kRec = kMitmMaxGrid * kMitmWaves / kMitmThreads;   // wave records per thread
-    unsigned long long x[kRec] = {};
+    unsigned long long x[kRec] = {}, rest = 0ull;   // the thread's records: largest keys; largest key not handed on
     WaveList<NS> Q;   // wave 0: the largest bounds of all workgroups
     wl_init(Q);
     if (grid > 1) {
@@ -593,8 +593,13 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
 #pragma unroll
         for (int q = 0; q < kRec; q++) {
             const uint32_t w = (uint32_t)(q * kMitmThreads + tid);
-            if (w < n_waves) x[q] = a.wg_lists[(uint64_t)w * (a.list + 1)];
+            unsigned long long y = 0ull;
+            if (w < n_waves) {
+                x[q] = a.wg_lists[(uint64_t)w * (a.list + 1)];
+                y = a.wg_lists[(uint64_t)w * (a.list + 1) + a.list];
+            }
             best = x[q] > best ? x[q] : best;
+            rest = y > rest ? y : rest;
         }
         tv = tf = 0;
         if (tid < grid) {
@@ -638,19 +643,19 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
         if (at < kMitmCand) s_cand[at] = 0xFFFFFFu - (uint32_t)(key & 0xFFFFFFull);
     };
     if (grid > 1) {
+        // a lane's third key is in no list, so a wave may have kept back a key
+        // above some that it handed on: the rest is tested whatever the list
+        // holds
+        if (rest >= cut) atomicOr(&s_bad, 1u);
 #pragma unroll
         for (int q = 0; q < kRec; q++) {
-            // the wave's keys from the cut up; its last value stands for
-            // those it did not hand on
+            // the wave's keys from the cut up
             const unsigned long long *rec = a.wg_lists + (uint64_t)(q * kMitmThreads + tid) * (a.list + 1);
             unsigned long long key = x[q];
-            for (int t = 0; key >= cut; ) {
+            for (int t = 1; key >= cut; t++) {
                 take(key);
-                key = rec[++t];
-                if (t == a.list) {
-                    if (key >= cut) atomicOr(&s_bad, 1u);
-                    break;
-                }
+                if (t == a.list) break;
+                key = rec[t];
             }
         }
     } else if (wv == 0) {

@@ -166,3 +166,79 @@ def test_mitm_static_matches_general_scan(mf, n_options, steps):
             a = p.search_static(*args, k=k, lo=lo, hi=hi, objective=ob)
             same(a, p.search_static(*args, k=k, lo=lo, hi=hi, objective=ob, dump=True))
     p.close()
+
+
+# ---- searches of more than 4,096 prefixes, by many workgroups
+
+def separable(n_options, good=None, cap=None, seed=0):
+    """An instance whose predictions are columns of the option row (latency
+    column 6: 0 for the options of `good`, 1 for the others, bound 0.5;
+    throughput column 7), every value on the 2^-14 grid: sums are exact in any
+    order, so the whole space can be enumerated in integers."""
+    inst = synth.make_instance(n_options, 8, 4, 32, 32, seed=seed, vram_quantile=0.6)
+    if cap is not None:
+        inst = replace(inst, vram_cap=cap)
+    f = inst.features
+    f[:, 6] = 0.0 if good is None else 1.0
+    f[:, 7] += 1.0
+    for i, off in enumerate(inst.option_offsets):
+        if good is not None:
+            f[off + np.asarray(good[i]), 6] = 0.0
+        W1, b1, W2, b2, W3, b3 = inst.model_weights(i)
+        for a in (W1, b1, W2, b2, W3, b3):
+            a[:] = 0.0
+        W1[0, 6] = W1[1, 7] = W2[0, 0] = W2[1, 1] = W3[0, 0] = W3[1, 1] = 1.0
+    return replace(inst, sla=np.full(inst.n_models, 0.5, np.float32))
+
+
+def enumerate_separable(inst, omega, lo, hi, k):
+    """Counts and top-k of a separable instance (whole-number weights) over
+    [lo, hi) by integer sums over every configuration, in torch."""
+    import torch
+    K = [int(x) for x in inst.n_options]
+    j0, S = len(K), 1
+    while j0 > 0 and S * K[j0 - 1] <= 1 << 22:
+        j0 -= 1
+        S *= K[j0]
+
+    def sums(models):
+        v = torch.zeros(1, dtype=torch.int64, device="cuda")
+        J, ok = v.clone(), torch.ones(1, dtype=torch.bool, device="cuda")
+        for i in models:
+            r = inst.features[inst.option_offsets[i]:inst.option_offsets[i] + K[i]].astype(np.float64)
+            col = lambda c, w: torch.as_tensor(np.rint(r[:, c] * w * 2 ** 14).astype(np.int64), device="cuda")
+            v = (v[:, None] + col(synth.COL_VRAM, 1.0)).flatten()
+            J = (J[:, None] + col(7, float(omega[i]))).flatten()
+            ok = (ok[:, None] & (col(6, 1.0) == 0)).flatten()
+        return v, J, ok
+
+    cap = int(np.floor(float(inst.vram_cap) * 2 ** 14))
+    (pv, pJ, pok), (sv, sJ, sok) = sums(range(j0)), sums(range(j0, len(K)))
+    u = torch.arange(S, device="cuda")
+    n_vram = n_feas = 0
+    best = torch.empty(0, dtype=torch.int64, device="cuda")   # J 2^34 - index: one integer orders by (J, -index)
+    for p in range(lo // S, (hi - 1) // S + 1):
+        vram = (sv + pv[p] <= cap) & (u >= lo - p * S) & (u < hi - p * S)
+        feas = vram & sok & pok[p]
+        n_vram += int(vram.sum())
+        n_feas += int(feas.sum())
+        key = torch.where(feas, ((sJ + pJ[p]) << 34) - (u + p * S), torch.iinfo(torch.int64).min)
+        best = torch.cat([best, key])
+        best = torch.topk(best, min(k, len(best)))[0]
+    best = best[best > torch.iinfo(torch.int64).min].cpu().numpy()
+    J = -(-best >> 34)                                        # rounded up: the index was subtracted
+    return dict(n_eval=hi - lo, n_vram=n_vram, n_feas=n_feas, top_idx=((J << 34) - best).astype(np.uint64),
+                top_J=J.astype(np.float64) * 2.0 ** -14)
+
+
+@pytest.mark.gpu
+def test_mitm_few_feasible_prefixes_of_many(mf):
+    # 2^20 prefixes, four to a lane, of which 64 are feasible, laid out so that
+    # some lanes hold three or four of them and their waves few others
+    good = [[0, 4, 8, 12], [0], [0, 8, 1, 10], [0, 12, 8, 4], [0], [0], [0], [0]]
+    inst = separable([16] * 8, good, cap=1e4)
+    p = mf.Problem(inst)
+    a = p.search(inst.sla, inst.omega, k=64, state=synth.make_state(inst, 1))
+    p.close()
+    assert a["n_feas"] == 64 and len(a["top_idx"]) == 64
+    same(a, enumerate_separable(inst, inst.omega, 0, inst.space_size, 64))

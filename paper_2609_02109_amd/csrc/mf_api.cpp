@@ -611,11 +611,15 @@ WsLayout ws_layout(const mf_problem &p, uint64_t n, int top_k, uint32_t worklist
     w.small = !p.bf_ok && n <= kSmallRange && w.grid < 512;
     w.seg_cap = w.small ? (uint32_t)(((uint64_t)w.work_cap + w.grid - 1) / w.grid) : 0;
     w.eval_top = std::min(w.kp, std::max(std::max(4, top_k / 2 + 1), (2 * top_k + w.grid - 1) / w.grid + 2));
-    // spread: the best lie over the workgroups as if at random, about m = 1.5
-    // top_k / grid each; m + 6 sqrt(m) + 3 are exceeded with probability below
-    // 1e-5 (the fallback pass then runs).  At k = 16 over 206 workgroups 6
-    // entries instead of 9: one round of canonical forwards instead of two
-    // (the fast kernel 33.1 -> 27.2 us at 105,435 configurations, k = 16).
+    // spread: the range is dealt so that the best lie over the workgroups as
+    // if at random, whatever the option counts (FastArgs::spread), about m =
+    // 1.5 top_k / grid each; of balls thrown at random, more than m + 6 sqrt(m)
+    // + 3 in one of 256 workgroups have a probability below 1e-5 (the fallback
+    // pass then runs).  At k = 16 over 206 workgroups 6 entries instead of 9:
+    // one round of canonical forwards instead of two (the fast kernel 33.1 ->
+    // 27.2 us at 105,435 configurations, k = 16).  Dealt without the hash the
+    // best of equal power-of-two counts met in few workgroups: 16^5, k = 16 took
+    // the fallback pass, 287 us against 131.
     w.spread = w.small && w.grid > 1 && p.space <= (1ull << 32);
     const double m = 1.5 * top_k / w.grid;
     w.eval_spread = std::min(w.kp, (int)std::ceil(m + 6.0 * std::sqrt(m) + 3.0));
@@ -834,7 +838,7 @@ mf_status run_range(mf_problem *p, const mf_search_args *args, uint64_t lo, uint
         fa.vram_slot = p->vram_slot;
         // neighbours to different workgroups (a dump's stores want them
         // together)
-        fa.spread = w.spread && !dump ? (uint32_t)((n + 31) / 32) : 0u;
+        fa.spread = w.spread && !dump ? (uint32_t)((n + w.grid - 1) / w.grid) : 0u;
         FinishArgs fin{};
         fin.res = R;
         fin.res_host = ev.host_result();

@@ -836,6 +836,19 @@ scan_kernel(const FastArgs args, const FastConst fc, const int mode, const int k
     }
 }
 
+// Where round h of a dealt range begins among n workgroups: a hash of h, so
+// that configurations a whole number of rounds apart (the options of a model,
+// where the counts are powers of two) do not meet in one workgroup.
+__device__ __forceinline__ uint32_t deal_rotation(uint32_t h, uint32_t n)
+{
+    h ^= h >> 16;
+    h *= 0x85EBCA6Bu;
+    h ^= h >> 13;
+    h *= 0xC2B2AE35u;
+    h ^= h >> 16;
+    return __umulhi(h, n);
+}
+
 // Small ranges: a tile of 32 configurations per wave (latency counts here, so
 // the range goes to as many waves as there are tiles), then the certification.
 template <int MAXN, int A, int H, int WAVES, bool OBJ, bool SIG>
@@ -890,7 +903,7 @@ small_kernel(const FastArgs args, const FastConst fc, const int kp)
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));   // wave-uniform
     const int gw = blockIdx.x * WAVES + wv;
     const uint64_t n = args.n;
-    const uint64_t n_tiles = (n + 31) >> 5;
+    const uint32_t n_tiles = ((spread ? spread : (uint32_t)n) + 31) >> 5;   // n <= 2^20
 
     uint32_t bd[MAXN] = {};
     if (spread == 0u) {
@@ -911,9 +924,14 @@ small_kernel(const FastArgs args, const FastConst fc, const int kp)
     wl_init(wl);
     uint32_t c_vram = 0, c_feas = 0;
 
-    for (uint64_t tile = gw; tile < n_tiles; tile += (uint64_t)args.total_waves) {
-        const uint64_t off = spread ? (uint64_t)((uint32_t)col * spread + (uint32_t)tile)
-                                         : tile * 32u + (uint64_t)col;
+    const uint32_t tile_step = spread ? (uint32_t)WAVES : (uint32_t)args.total_waves;
+    for (uint32_t tile = spread ? wv : gw; tile < n_tiles; tile += tile_step) {
+        uint32_t o = tile * 32u + (uint32_t)col;   // in order, or the round
+        if (spread) {
+            const uint32_t at = (uint32_t)blockIdx.x + deal_rotation(o, gridDim.x);
+            o = o < spread ? o * gridDim.x + (at < gridDim.x ? at : at - gridDim.x) : 0xFFFFFFFFu;
+        }
+        const uint64_t off = o;
         const bool valid = off < n;
         uint32_t d[MAXN];
         if (spread) {

@@ -188,10 +188,12 @@ uint32_t digits[kMaxN];     // mixed-radix digits, small ranges: of total_waves 
     const float *features;      // [sumK][n_local]
     const int32_t *agg_cols;    // [A] (original slot order)
     int n_local, vram_slot;
-    // > 0: configuration t of the range is column t / spread of tile t %
-    // spread (spread = the number of tiles): neighbours, which share most
-    // options and so rank together, go to different workgroups.  The range
-    // lies below 2^32.  0: tile t / 32.
+    // > 0: the range is dealt to the workgroups in rounds, a configuration to
+    // each: workgroup g of G holds configuration h G + (g + r_h) mod G of
+    // round h < spread = ceil(n / G), r_h a hash of h.  Neighbours, which share
+    // most options and so rank together, go to different workgroups, and those
+    // whole rounds apart as if at random.  The range lies below 2^32.
+    // 0: in order, 32 to a tile.
     uint32_t spread;
 };
 

@@ -47,3 +47,25 @@ def test_dealt_ranges(mf, K, H, k, lo, n, flat):
     assert a["n_vram"] == b["n_vram"] and a["n_feas"] == b["n_feas"]
     np.testing.assert_array_equal(a["top_idx"], b["top_idx"])
     assert a["top_J"].tobytes() == b["top_J"].tobytes()
+
+
+@pytest.mark.parametrize("K", [(16,) * 4, (8,) * 5, (32,) * 3, (8,) * 6, (16,) * 5])
+@pytest.mark.parametrize("k", [16, 64])
+def test_dealt_ranges_of_equal_counts(mf, K, k):
+    """Where every option count is the same power of two, and one model weighs
+    little, the best configurations lie at regular distances.  The dealing has
+    to spread them all the same: no workgroup may hold so many of them that the
+    search needs its fallback pass."""
+    inst = synth.make_instance(list(K), 8, 4, 32, 32, seed=1, vram_quantile=0.75)
+    p = mf.Problem(inst)
+    for light in (None, *range(len(K) - 1)):
+        om = np.ones(len(K), np.float32)
+        if light is not None:
+            om[light] = 0.02
+        a = p.search(inst.sla, om, k=k)
+        b = p.search(inst.sla, om, k=k, dump=True)
+        assert a["n_topk_collect"] == 0, light
+        assert a["n_vram"] == b["n_vram"] and a["n_feas"] == b["n_feas"]
+        np.testing.assert_array_equal(a["top_idx"], b["top_idx"])
+        assert a["top_J"].tobytes() == b["top_J"].tobytes()
+    p.close()

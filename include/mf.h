@@ -236,8 +236,10 @@ typedef struct {
     int32_t n_splits;          /* range splits forced by a full certification list */
     uint64_t top_idx[MF_MAX_TOPK];  /* joint indices; UINT64_MAX past n_top */
     double top_J[MF_MAX_TOPK];      /* canonical J; -inf past n_top */
-    float main_kernel_ms;      /* HIP-event time of the fast search kernel(s) on `stream` */
-    float pad;
+    float main_kernel_ms;      /* time of the search kernel(s) on `stream`: HIP events, or the kernel's own clock */
+    uint32_t n_scans;          /* fixed-state and static searches: launches of the scan over every configuration
+                                  (a dump or mask was asked for, or the meet in the middle left it a range);
+                                  0 when the meet in the middle answered alone, and for all other searches */
 } mf_result;
 
 /* Bytes of device workspace mf_search needs for these arguments. */

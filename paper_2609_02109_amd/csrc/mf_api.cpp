@@ -674,6 +674,7 @@ void merge_into(mf_result &acc, const mf_result &part, int k)
     acc.n_topk_collect += part.n_topk_collect;
     acc.n_splits += part.n_splits;
     acc.main_kernel_ms += part.main_kernel_ms;
+    acc.n_scans += part.n_scans;
     std::vector<std::pair<double, uint64_t>> v;
     for (int q = 0; q < acc.n_top; q++) v.push_back({acc.top_J[q], acc.top_idx[q]});
     for (int q = 0; q < part.n_top; q++) v.push_back({part.top_J[q], part.top_idx[q]});
@@ -1314,6 +1315,7 @@ mf_status search_fixed(mf_problem *p, const mf_search_args *args, char *ws, hipS
             part.top_J[q] = h.top_J[q];
         }
         part.main_kernel_ms = ms;
+        part.n_scans = 1;
         merge_into(acc, part, args->top_k);
         lo += n;
     }
@@ -1461,6 +1463,7 @@ mf_status search_static(mf_problem *p, const mf_static_args *args, char *ws, hip
             part.top_J[q] = h.top_J[q];
         }
         part.main_kernel_ms = ms;
+        part.n_scans = 1;
         merge_into(acc, part, args->top_k);
         lo += n;
     }

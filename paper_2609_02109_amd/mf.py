@@ -89,7 +89,7 @@ class Result(C.Structure):
                 ("n_flagged", C.c_uint64), ("n_topk_collect", C.c_uint64),
                 ("n_top", C.c_int32), ("n_splits", C.c_int32),
                 ("top_idx", C.c_uint64 * MAX_TOPK), ("top_J", C.c_double * MAX_TOPK),
-                ("main_kernel_ms", C.c_float), ("pad", C.c_float)]
+                ("main_kernel_ms", C.c_float), ("n_scans", C.c_uint32)]
 
 
 MAX_STEPS = 32
@@ -311,7 +311,8 @@ class Problem:
         nt = int(res.n_top)
         out = dict(n_eval=int(res.n_eval), n_vram=int(res.n_vram), n_feas=int(res.n_feas),
                    n_flagged=int(res.n_flagged), n_topk_collect=int(res.n_topk_collect),
-                   n_splits=int(res.n_splits), main_kernel_ms=float(res.main_kernel_ms),
+                   n_splits=int(res.n_splits), n_scans=int(res.n_scans),
+                   main_kernel_ms=float(res.main_kernel_ms),
                    top_idx=np.array(res.top_idx[:nt], np.uint64),
                    top_J=np.array(res.top_J[:nt], np.float64))
         if dump:
@@ -342,7 +343,7 @@ class Problem:
         _check(lib.mf_search_static(self.handle, C.byref(args), _ptr(ws), C.c_size_t(ws.numel()), _stream(stream),
                                     C.byref(res)), "mf_search_static")
         nt = int(res.n_top)
-        out = dict(n_eval=int(res.n_eval), n_vram=int(res.n_vram), n_feas=int(res.n_feas),
+        out = dict(n_eval=int(res.n_eval), n_vram=int(res.n_vram), n_feas=int(res.n_feas), n_scans=int(res.n_scans),
                    main_kernel_ms=float(res.main_kernel_ms), top_idx=np.array(res.top_idx[:nt], np.uint64),
                    top_J=np.array(res.top_J[:nt], np.float64))
         if dump:

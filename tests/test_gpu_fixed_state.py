@@ -10,6 +10,7 @@ the full sizes (the whole joint space) the exact counts come from an
 independent meet-in-the-middle count over the oracle's per-option values,
 and the top-k from the oracle's evaluation of the returned indices.
 """
+import math
 from dataclasses import replace
 
 import numpy as np
@@ -69,10 +70,10 @@ def test_fixed_eq3_n5_full(mf, orc, seed):
     assert r["n_feas"] > 0
 
 
-# Shapes whose last two models form the scanned inner block with a periodic
-# last digit (its option count 3 x 2^j, 128 or 2^j): whole-space searches
-# without a dump take the scan that keeps each lane's rows of the last model
-# in registers.  Counts, top-k indices and canonical J against the oracle.
+# Shapes whose last two models form an inner block with a periodic last digit
+# (its option count 3 x 2^j, 128 or 2^j).  The meet in the middle answers these
+# searches; the scan's kernels for such blocks are under test below.  Counts,
+# top-k indices and canonical J against the oracle.
 # (instance seeds with feasible configurations under both objectives)
 @pytest.mark.parametrize("n_options,period,seed", [([5, 16, 24], 3, 0), ([3, 2, 128], 2, 3), ([7, 16, 16], 1, 0),
                                                    ([2, 4, 8, 48], 3, 0), ([5, 24, 24], 3, 0), ([3, 16, 32], 1, 0)])
@@ -93,10 +94,8 @@ def test_fixed_periodic_last_digit(mf, orc, n_options, period, seed, eq3):
     assert g["top_J"].tobytes() == r["top_J"].tobytes()
 
 
-# Whole spaces of 6-9 million configurations with a periodic last digit:
-# several blocks per wave, so a wave's list fills and the later blocks whose
-# largest possible J falls under its k-th J form only the counts.  Any block
-# skipped wrongly would drop a configuration of the oracle's exact top-k.
+# Whole spaces of 6-9 million configurations with a periodic last digit, by the
+# meet in the middle.
 @pytest.mark.parametrize("n_options", [[24, 32, 32, 16, 16], [16, 32, 32, 24, 24]])
 @pytest.mark.parametrize("eq3", [False, True])
 def test_fixed_periodic_pruned_blocks(mf, orc, n_options, eq3):
@@ -111,6 +110,50 @@ def test_fixed_periodic_pruned_blocks(mf, orc, n_options, eq3):
     r = orc.Problem(inst, ob, state=state).search(inst.sla, inst.omega, k=k, lo=0, hi=inst.space_size)
     assert g["n_vram"] == r["n_vram"] and g["n_feas"] == r["n_feas"]
     assert r["n_feas"] > 100_000
+    np.testing.assert_array_equal(g["top_idx"], r["top_idx"])
+    assert g["top_J"].tobytes() == r["top_J"].tobytes()
+
+
+# The scan without a dump: the first two models weigh nothing and take the same
+# VRAM, so 1,056 prefixes and more tie at the best value, more than the meet in
+# the middle takes, and it leaves the range to the scan.  Every form for blocks
+# with a periodic last digit (unrolled and looped groups, one to three phases),
+# the lane-constant digit (a range that ends inside a block), two and four inner
+# models.  With a third outer model several blocks go to a wave, its list fills
+# and later blocks whose largest possible J falls under its k-th J form only the
+# counts: any block skipped wrongly would drop one of the oracle's top-k.
+@pytest.mark.parametrize("rest,ragged", [([16, 16], False), ([24, 24], False), ([16, 24], False), ([2, 128], False),
+                                         ([16, 32], False), ([16, 16], True), ([17, 19], False), ([5, 4, 5, 3], False),
+                                         ([24, 16, 16], False), ([16, 24, 24], False)])
+@pytest.mark.parametrize("eq3", [False, True])
+def test_fixed_scan_without_dump(mf, orc, rest, ragged, eq3):
+    lead = [48, 32] if len(rest) == 3 else [33, 32]
+    inst = synth.make_instance(lead + rest, 8, 4, 32, 32, seed=0, vram_quantile=0.7)
+    inst.features[:sum(lead), synth.COL_VRAM] = 2.0
+    inst.omega[:2] = 0.0
+    # the cap at the 0.7 quantile of the sums, the latency bounds at the 0.8 quantile of the options'
+    inst = replace(inst, vram_cap=float(np.quantile(sum(np.random.default_rng(0).choice(
+        inst.features[o:o + k, synth.COL_VRAM], 9999) for o, k in zip(inst.option_offsets, inst.n_options)), 0.7)))
+    state = synth.make_state(inst, 3)
+    for i, (o, K) in enumerate(zip(inst.option_offsets, inst.n_options)):
+        one = np.arange(K) * math.prod(int(x) for x in inst.n_options[i + 1:])
+        lat = orc.Problem(inst, state=state).eval_list(one.astype(np.uint64), inst.sla, inst.omega)["lat"][:, i]
+        inst.sla[i] = np.inf if i < 2 else np.quantile(lat, 0.8)
+    ob = synth.make_objective(inst, 3, tau_range=(-0.6, -0.2)) if eq3 else None
+    if eq3:
+        ob.tau[:2] = -np.inf
+        ob.prev_variant[:2] = -1
+    n = inst.space_size
+    lo, hi = (5, n - 7) if ragged else (0, n)
+    k = 8
+    print(f"[fixed scan] K={lead + rest} [{lo},{hi}) eq3={eq3}", flush=True)
+    p = mf.Problem(inst, variants=ob)
+    g = p.search(inst.sla, inst.omega, k=k, lo=lo, hi=hi, objective=ob, state=state)
+    p.close()
+    r = orc.Problem(inst, ob, state=state).search(inst.sla, inst.omega, k=k, lo=lo, hi=hi)
+    assert g["n_scans"] == 1
+    assert g["n_vram"] == r["n_vram"] and g["n_feas"] == r["n_feas"]
+    assert 0 < r["n_feas"] < r["n_vram"] < n
     np.testing.assert_array_equal(g["top_idx"], r["top_idx"])
     assert g["top_J"].tobytes() == r["top_J"].tobytes()
 

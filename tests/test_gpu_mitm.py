@@ -1,9 +1,11 @@
 """The separable searches by meet in the middle (fixed-state and static,
 without a dump) against the general scan of the same library (the same call
-with a dump, which the oracle pins elsewhere): counts, top-k indices and
-canonical J bit for bit, over the splits, ranges and values where the two
-could differ.  The inversion of the rounded VRAM additions is checked on the
-CPU against the additions themselves."""
+with a dump, which the oracle pins elsewhere) and, where a space is too large
+for a dump, against an enumeration in whole numbers: counts, top-k indices and
+canonical J bit for bit, over the splits, ranges and values where they could
+differ.  n_scans tells which path answered.  The inversion of the rounded VRAM
+additions is checked on the CPU against the additions themselves."""
+import math
 import os
 import subprocess
 from dataclasses import replace
@@ -97,8 +99,10 @@ def negative_vram(inst):
     inst.features[:, synth.COL_VRAM] -= 15.0
 
 
-def huge_vram(inst):   # sums that overflow to infinity
+def huge_vram(inst):   # sums that overflow to infinity (the surrogates do not see the column)
     inst.features[::3, synth.COL_VRAM] = 3e38
+    for i in range(inst.n_models):
+        inst.model_weights(i)[0][:, synth.COL_VRAM] = 0.0
 
 
 def tied(inst):        # every configuration's J equal
@@ -108,7 +112,8 @@ def tied(inst):        # every configuration's J equal
 
 
 # one model; the largest option count; single options; suffixes of exactly
-# 64, 4,096 and just past; one workgroup and many; more than eight models
+# 64, 4,096 and just past; more than eight models.  All of one workgroup (up
+# to 4,096 prefixes); larger grids are below
 SHAPES = [([5], None), ([255], None), ([3, 1, 1, 5], None), ([2] * 6, None), ([2] * 12, None), ([2] * 13, None),
           ([63, 65], None), ([255, 20], None), ([7, 11, 5, 9], negative_vram), ([9, 8, 7, 6], huge_vram),
           ([9, 10, 8], tied), ([13, 16, 16, 17], None), ([4] * 9, None), ([24, 24, 24, 24], None), ([130, 131], None)]
@@ -129,6 +134,8 @@ def test_mitm_matches_general_scan(mf, n_options, edit, eq3):
             a = p.search(inst.sla, inst.omega, k=k, lo=lo, hi=hi, objective=ob, state=st)
             b = p.search(inst.sla, inst.omega, k=k, lo=lo, hi=hi, objective=ob, state=st, dump=True)
             same(a, b)
+            assert b["n_scans"] == 1
+            assert a["n_scans"] == 0 or edit is tied
     p.close()
 
 
@@ -164,7 +171,9 @@ def test_mitm_static_matches_general_scan(mf, n_options, steps):
             print(f"[mitm static] {n_options} T={steps} [{lo},{hi}) k={k}", flush=True)
             args = (sc.states[0], sc.sla[0], sc.omega[0])
             a = p.search_static(*args, k=k, lo=lo, hi=hi, objective=ob)
-            same(a, p.search_static(*args, k=k, lo=lo, hi=hi, objective=ob, dump=True))
+            b = p.search_static(*args, k=k, lo=lo, hi=hi, objective=ob, dump=True)
+            same(a, b)
+            assert a["n_scans"] == 0 and b["n_scans"] == 1
     p.close()
 
 
@@ -197,7 +206,7 @@ def enumerate_separable(inst, omega, lo, hi, k):
     import torch
     K = [int(x) for x in inst.n_options]
     j0, S = len(K), 1
-    while j0 > 0 and S * K[j0 - 1] <= 1 << 22:
+    while j0 > 0 and S * K[j0 - 1] <= 1 << 24:
         j0 -= 1
         S *= K[j0]
 
@@ -231,6 +240,19 @@ def enumerate_separable(inst, omega, lo, hi, k):
                 top_J=J.astype(np.float64) * 2.0 ** -14)
 
 
+def prefixes(n_options):
+    """Prefixes of the split (models before the suffix kept in LDS)."""
+    space, S, left = math.prod(n_options), 1, math.prod(n_options)
+    for j in range(len(n_options) - 1, -1, -1):
+        S *= n_options[j]
+        if S > 4096:
+            break
+        left = space // S
+        if left <= 1024 or (left <= 1 << 18 and (j == 0 or S * n_options[j - 1] > 1024)):
+            break
+    return left
+
+
 @pytest.mark.gpu
 def test_mitm_few_feasible_prefixes_of_many(mf):
     # 2^20 prefixes, four to a lane, of which 64 are feasible, laid out so that
@@ -242,3 +264,67 @@ def test_mitm_few_feasible_prefixes_of_many(mf):
     p.close()
     assert a["n_feas"] == 64 and len(a["top_idx"]) == 64
     same(a, enumerate_separable(inst, inst.omega, 0, inst.space_size, 64))
+
+
+# 8 to 46 workgroups, a ragged last one, more than eight models
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_options", [[20] * 5, [9] * 7, [11, 13, 17, 5, 9, 23], [6] * 9], ids=lambda k: "x".join(map(str, k)))
+@pytest.mark.parametrize("eq3", [False, True])
+def test_mitm_many_workgroups(mf, n_options, eq3):
+    assert prefixes(n_options) > 4096
+    inst = instance(n_options, seed=3)
+    n = inst.space_size
+    ob = synth.make_objective(inst, 3, tau_range=(-0.4, 0.3)) if eq3 else None
+    st = synth.make_state(inst, 5)
+    p = mf.Problem(inst, variants=ob)
+    for lo, hi in ((0, n), (n // 7 + 5, n - n // 9 - 1)):
+        for k in (1, 33, 64):
+            print(f"[mitm grid] {n_options} eq3={eq3} [{lo},{hi}) k={k}", flush=True)
+            a = p.search(inst.sla, inst.omega, k=k, lo=lo, hi=hi, objective=ob, state=st)
+            same(a, p.search(inst.sla, inst.omega, k=k, lo=lo, hi=hi, objective=ob, state=st, dump=True))
+            assert a["n_scans"] == 0
+    p.close()
+
+
+# one and two prefixes to a lane (331,776), four (2^20), 32 (8.4 million, and a
+# range that takes two launches); the last with a clustered half of the options
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_options,launches,half", [([24] * 6, 1, False), ([16] * 8, 1, False),
+                                                     ([33, 32, 32, 255, 17], 2, False), ([16] * 8, 1, True)],
+                         ids=lambda x: "x".join(map(str, x)) if isinstance(x, list) else str(x))
+@pytest.mark.parametrize("ragged", [False, True])
+def test_mitm_spaces_of_many_prefixes(mf, n_options, launches, half, ragged):
+    per = prefixes(n_options)
+    assert per > 1 << 18 and (per + (1 << 23) - 1) >> 23 == launches
+    good = [range(k // 2) for k in n_options] if half else None
+    inst = separable(n_options, good, seed=2)
+    n = inst.space_size
+    lo, hi = (n // 200 + 7, n - n // 300 - 5) if ragged else (0, n)
+    p = mf.Problem(inst)
+    for omega in (np.ones(len(n_options)), np.arange(len(n_options)) - 1.0):   # the second: -1, 0, 1, 2, ...
+        omega = omega.astype(np.float32)
+        want = enumerate_separable(inst, omega, lo, hi, 64)
+        for k in (1, 33, 64):
+            print(f"[mitm space] {n_options} [{lo},{hi}) omega={omega} k={k}", flush=True)
+            a = p.search(inst.sla, omega, k=k, lo=lo, hi=hi, state=synth.make_state(inst, 1))
+            same(a, dict(want, top_idx=want["top_idx"][:k], top_J=want["top_J"][:k]))
+            assert a["n_scans"] == 0
+    p.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("steps", [1, 7])
+def test_static_scan_without_mask(mf, orc, steps):
+    # 1,280 prefixes that tie (the first two models weigh nothing): more than
+    # the meet in the middle takes, so the scan answers, without a mask
+    inst = synth.make_instance([40, 32, 7, 6, 5], 8, 4, 64, 32, seed=4, vram_quantile=0.7, act="sigmoid", quantise=False)
+    inst.features[:72, synth.COL_VRAM] = 2.0
+    sc = synth.make_scenarios(inst, 1, steps, seed=4)
+    om = sc.omega[0].copy()
+    om[:, :2] = 0.0
+    g = mf.Problem(inst).search_static(sc.states[0], sc.sla[0], om, k=9)
+    r = orc.static_search(inst, None, sc.states[0], sc.sla[0], om, k=9)
+    assert g["n_scans"] == 1
+    assert g["n_vram"] == r["n_vram"] and g["n_feas"] == r["n_feas"]
+    np.testing.assert_array_equal(g["top_idx"], r["top_idx"])
+    assert g["top_J"].tobytes() == r["top_J"].tobytes()

@@ -356,6 +356,7 @@ __global__ void __launch_bounds__(kRunMaxThreads) ga_run_kernel(const GARunArgs 
     if (r.g0 < r.g1) fetch(r.g0);
 
     // ---- the first generation's population and its fitness
+    double slot0 = 0.0;   // thread 0: the fitness in slot 0
     double ef = -INFINITY;
     uint32_t ei = 0xFFFFFFFFu;
     auto offer = [&](double f, uint32_t x) {   // the lane's best (f desc, index asc)
@@ -376,6 +377,7 @@ __global__ void __launch_bounds__(kRunMaxThreads) ga_run_kernel(const GARunArgs 
         const double f = fitness(x, d);
         idx[j] = x;
         fit[j] = f;
+        if (j == 0) slot0 = f;
 #pragma unroll
         for (int w = 0; w < DW; w++) dig[j * DW + w] = d[w];
         offer(f, x);
@@ -486,7 +488,10 @@ __global__ void __launch_bounds__(kRunMaxThreads) ga_run_kernel(const GARunArgs 
                 bestJ = f;
                 bestI = (uint64_t)x;
             }
-            if (tid == 0 && !last) {
+            // slot 0 goes to the elite.  A NaN there stays (nothing compares
+            // above it), also when every fitness is NaN and x is no index
+            if (tid == 0 && !last && slot0 == slot0) {
+                slot0 = f;
                 fit[0] = f;
                 idx[0] = x;
                 uint64_t d[DW];

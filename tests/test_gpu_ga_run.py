@@ -67,3 +67,29 @@ def test_ga_run_spans_of_draws(mf, orc):
     r = orc.Problem(inst).ga(sc.sla, sc.omega, final_pop=True, **kw)
     np.testing.assert_array_equal(g["best_idx"], r["best_idx"])
     np.testing.assert_array_equal(g["final_pop"].cpu().numpy().astype(np.uint64), r["final_pop"])
+
+
+# weights that are not finite: every fitness of a scenario NaN, or some of them,
+# or infinite.  The elite is slot 0 when its fitness is NaN; the last case
+# carries it from launch to launch
+@pytest.mark.parametrize("fixed", [True, False])
+@pytest.mark.parametrize("S,kw", [(6, dict(pop=200, gens=6)), (6, dict(pop=300, gens=1)), (40, dict(pop=3000, gens=25))])
+def test_ga_run_not_finite_fitness(mf, orc, fixed, S, kw):
+    inst = synth.make_instance([6, 5, 7, 4], 8, 4, 32, 32, seed=3, vram_quantile=0.7)
+    sc = synth.ga_scenarios(4, S, seed=3)
+    sla, om = np.full_like(sc.sla, np.inf), sc.omega.copy()
+    om[0] = np.nan
+    om[1, :2] = np.inf            # inf - inf where their throughputs differ in sign
+    om[2, 0], om[2, 1] = np.inf, -np.inf
+    om[3, 2] = -np.inf
+    sla[4] = np.nan               # nothing feasible
+    st = synth.make_state(inst, 3) if fixed else None
+    print(f"[ga run] not finite fixed={fixed} {kw}", flush=True)
+    g = mf.Problem(inst).ga(sla, om, seed=5, p_mut=0.1, final_pop=True, state=st, **kw)
+    with np.errstate(invalid="ignore"):
+        r = orc.Problem(inst, state=st).ga(sla, om, seed=5, p_mut=0.1, final_pop=True, **kw)
+    pop = g["final_pop"].cpu().numpy().astype(np.uint64)
+    assert (pop < inst.space_size).all()
+    np.testing.assert_array_equal(pop, r["final_pop"])
+    np.testing.assert_array_equal(g["best_idx"], r["best_idx"])
+    assert g["best_J"].tobytes() == r["best_J"].tobytes()

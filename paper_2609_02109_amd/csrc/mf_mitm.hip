@@ -27,9 +27,10 @@
 // table in LDS (its own copy: cheaper than a launch that builds it once) and
 // its lanes take prefixes.  The last workgroup to finish (a ticket, no
 // waiting) takes the largest bounds the waves hand on, selects the candidate
-// prefixes, evaluates their hits and writes the result.  When a wave may have
-// kept back a prefix that reaches theta (many equal bounds), or a term is not
-// finite, the result says so and the host runs the general scan.
+// prefixes, evaluates their hits and writes the result.  When a wave of a grid
+// may have kept back a prefix that reaches theta (many equal bounds), when more
+// prefixes reach it than the last workgroup takes, or a term is not finite, the
+// result says so and the host runs the general scan.
 //
 // Bound by latency: some 15 dependent LDS phases of 2-4 us each, no unit busy.
 // Whole searches, call to host result, general scan before -> now (MI355X):
@@ -44,6 +45,14 @@ constexpr int kMitmThreads = 1024;
 constexpr int kMitmWaves = kMitmThreads / 64;
 constexpr int kMitmCand = 1024;      // candidate prefixes the last workgroup takes
 constexpr int kMitmHits = 512;       // configurations evaluated a thread each
+// One workgroup whose list is full of bounds that reach the cut (prefixes that
+// tie: models of no weight, equal options) takes its candidates from all its
+// prefixes again.  Where the tie goes through the suffixes too, every one of
+// them is a hit: beyond this many (about 2 ns each at 8 models) the search is
+// left to the scan.  12x12x9x9x9 with two models of no weight, k = 1: 107 us a
+// call; 140 when a full list goes to the scan, 127 for the scan alone.  Every J
+// equal (no model has a weight): 147 against 126, lost before the scan.
+constexpr uint32_t kMitmTieHits = 4096;
 
 // Dynamic LDS.  While the suffixes are built level by level, their thresholds
 // alternate between lst and G and their sums between M and Bs.
@@ -223,7 +232,7 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
     __shared__ uint32_t s_wcnt[kMitmWaves];
     __shared__ double s_theta;
     __shared__ unsigned long long s_cut;
-    __shared__ uint32_t s_last, s_ncand, s_bad, s_nhit;
+    __shared__ uint32_t s_last, s_ncand, s_bad, s_nhit, s_full;
     __shared__ unsigned long long s_hit[kMitmHits];
     __shared__ uint32_t s_cand[kMitmCand];
     __shared__ unsigned long long s_t0;
@@ -499,6 +508,15 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
     // largest of all the others: sorted lists of 128 in every wave and their merges took 70 of
     // 145 us at 2^20 prefixes.
     const int grid = (int)gridDim.x;
+    // a prefix's key: an upper bound of its best J, its order-preserving bits
+    // rounded up to 40, then the lowest prefix (0: no feasible suffix); pos
+    // suffixes meet the cap, g of them the service constraints too
+    auto prefix_key = [&](uint32_t p, uint32_t &pos, uint32_t &g) {
+        const Prefix x = mitm_prefix<MAXN>(a, s_m, l.rows, p);
+        pos = mitm_pos(l.key, spad, x.v);
+        g = (int32_t)x.fl >= 0 ? l.G[pos] : 0u;
+        return g ? (((ord_f64((x.B + l.M[pos]) + slack) >> 24) + 1) << 24) | (unsigned long long)(0xFFFFFFu - p) : 0ull;
+    };
     WaveList<NS> L;
     wl_init(L);
     unsigned long long cv = 0, cf = 0, m1 = 0ull, m2 = 0ull, m3 = 0ull;
@@ -511,17 +529,10 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
         const uint32_t r = grid > 1 ? round * n_waves + (gw + round * step) % n_waves : i0 * n_waves + gw * 64u + lane;
         unsigned long long key = 0ull;
         if (r < n_whole) {
-            const uint32_t p = a.whole_lo + r;
-            const Prefix x = mitm_prefix<MAXN>(a, s_m, l.rows, p);
-            const uint32_t pos = mitm_pos(l.key, spad, x.v);
+            uint32_t pos, g;
+            key = prefix_key(a.whole_lo + r, pos, g);
             cv += pos;
-            if ((int32_t)x.fl >= 0) {
-                const uint32_t g = l.G[pos];
-                cf += g;
-                // an upper bound of the prefix's best J, its order-preserving
-                // bits rounded up to 40
-                if (g) key = (((ord_f64((x.B + l.M[pos]) + slack) >> 24) + 1) << 24) | (unsigned long long)(0xFFFFFFu - p);
-            }
+            cf += g;
         }
         if (grid == 1) {
             wl_offer_bulk(L, key, lane, kp);
@@ -625,6 +636,9 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
             s_theta = w;
             s_cut = kth ? ((ord_f64(w) >> 24) + 1) << 24 : 1ull;
         }
+        // a full list whose last key reaches the cut may have dropped others
+        const unsigned long long last = readlane64(Q.s[NS - 1], 63);
+        if (lane == 0) s_full = grid == 1 && last >= s_cut ? 1u : 0u;
     }
     // the largest sum per 64 sorted positions
     for (uint32_t s = wv; s < (spad + 63) / 64; s += kMitmWaves) {
@@ -638,6 +652,7 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
     __syncthreads();
     const double theta = s_theta;
     const unsigned long long cut = s_cut;
+    const bool full = s_full != 0u;
     auto take = [&](unsigned long long key) {
         const uint32_t at = atomicAdd(&s_ncand, 1u);
         if (at < kMitmCand) s_cand[at] = 0xFFFFFFu - (uint32_t)(key & 0xFFFFFFull);
@@ -658,18 +673,20 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
                 key = rec[t];
             }
         }
+    } else if (full) {
+        for (uint32_t r = tid; r < n_whole; r += kMitmThreads) {
+            uint32_t pos, g;
+            const unsigned long long key = prefix_key(a.whole_lo + r, pos, g);
+            if (key >= cut) take(key);
+        }
     } else if (wv == 0) {
 #pragma unroll
         for (int j = 0; j < NS; j++)
-            if (Q.s[j] >= cut) {
-                take(Q.s[j]);
-                // a full list whose last key reaches the cut may have dropped others
-                if (j == NS - 1 && lane == 63) atomicOr(&s_bad, 1u);
-            }
+            if (Q.s[j] >= cut) take(Q.s[j]);
     }
     __syncthreads();
     const uint32_t ncand = s_ncand;
-    const bool general = ncand > kMitmCand || s_bad != 0u || !finite;   // the host runs the general scan
+    bool general = ncand > kMitmCand || s_bad != 0u || !finite;   // the host runs the general scan
     // a thread per candidate prefix: its VRAM sum's position and its sum
     double *cand_B = reinterpret_cast<double *>(l.lst);                     // [kMitmCand]
     uint32_t *cand_pos = reinterpret_cast<uint32_t *>(cand_B + kMitmCand);  // [kMitmCand]
@@ -688,6 +705,7 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
             const uint32_t pos = cand_pos[c];
             unsigned long long segs = __ballot((uint32_t)lane * 64u < pos && (B + s_segmax[lane]) + slack >= bar);
             while (segs) {
+                if (full && *(volatile uint32_t *)&s_nhit > kMitmTieHits) return;
                 const uint32_t i = ((uint32_t)__ffsll((long long)segs) - 1u) * 64u + lane;
                 segs &= segs - 1;
                 const bool hit = i < pos && l.Bs[i] > -INFINITY && (B + l.Bs[i]) + slack >= bar;
@@ -706,6 +724,7 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
     });
     __syncthreads();
     const uint32_t nhit = s_nhit;
+    general = general || (full && nhit > kMitmTieHits);
     const bool few = nhit <= kMitmHits && !parts;
     if (!general && few) {
         // every hit's canonical value: T = 1 a thread per hit; otherwise a

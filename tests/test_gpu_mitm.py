@@ -312,6 +312,36 @@ def test_mitm_spaces_of_many_prefixes(mf, n_options, launches, half, ragged):
     p.close()
 
 
+# prefixes that tie, in a search of one workgroup: the first `zero` models weigh
+# nothing and (flat) take the same VRAM.  Up to 1,024 of them are looked into;
+# more, or a tie that goes through the suffixes too, is the scan's
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_options,zero,flat,scans", [
+    ([12, 12, 9, 9, 9], 2, False, 0), ([12, 12, 9, 9, 9], 2, True, 0), ([32, 32, 8, 8, 8], 2, True, 0),
+    ([33, 32, 8, 8, 8], 2, True, 1), ([65, 60, 60], 1, True, 0), ([9, 10, 8], 3, False, 0),
+    ([12, 12, 9, 9, 9], 5, False, 1)])
+def test_mitm_prefixes_that_tie(mf, n_options, zero, flat, scans):
+    inst = instance(n_options, seed=5)
+    if flat:
+        inst.features[:sum(n_options[:zero]), synth.COL_VRAM] = 2.0
+        inst = replace(inst, vram_cap=inst.vram_cap - 2.0 * zero)
+    inst = replace(inst, sla=np.full(inst.n_models, np.inf, np.float32))
+    omega = (np.arange(len(n_options)) >= zero).astype(np.float32)
+    st = synth.make_state(inst, 5)
+    n = inst.space_size
+    p = mf.Problem(inst)
+    for lo, hi in ((0, n), (n // 50 + 1, n - n // 60)):
+        for k in (1, 33, 64):
+            print(f"[mitm tie] {n_options} zero={zero} flat={flat} [{lo},{hi}) k={k}", flush=True)
+            a = p.search(inst.sla, omega, k=k, lo=lo, hi=hi, state=st)
+            b = p.search(inst.sla, omega, k=k, lo=lo, hi=hi, state=st, dump=True)
+            same(a, b)
+            assert b["n_feas"] > 64
+            if (lo, hi) == (0, n):
+                assert a["n_scans"] == scans
+    p.close()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("steps", [1, 7])
 def test_static_scan_without_mask(mf, orc, steps):

@@ -1110,7 +1110,11 @@ FixedArgs fixed_base(const mf_problem *p, const mf_objective &objective, int top
 // The split: the shortest suffix that leaves at most 1,024 prefixes when it
 // holds at most 1,024 combinations (one workgroup, one prefix per lane), else
 // at most 2^18 prefixes (one per lane of the chip) when it holds at most
-// kMitmSuffixMax, else the longest one within kMitmSuffixMax.
+// kMitmSuffixMax, else the longest one within kMitmSuffixMax; never one whose
+// tables LDS does not hold beside the option rows (one model's always fit:
+// 255 suffixes beside at most 4,080 rows).  Far more prefixes than lanes still
+// beat the scan: 65^5, 17.9 million prefixes of 65 suffixes, 325 us against
+// 1,240 us.
 struct MitmSplit {
     int j0;
     uint32_t S, spad;
@@ -1124,7 +1128,11 @@ MitmSplit mitm_split(const mf_problem &p)
     for (int j = p.N - 1; j >= 0; j--) {
         S *= (uint64_t)p.K[j];
         if (S > kMitmSuffixMax) break;
+        uint32_t spad = best.spad;
+        while (spad < S) spad *= 2;
+        if (mitm_lds_bytes(p.sumK, spad) > kMitmLdsMax) break;
         best.j0 = j;
+        best.spad = spad;
         best.S = (uint32_t)S;
         best.prefixes = p.space / S;
         // stop as soon as the prefixes are few enough, unless a longer suffix
@@ -1132,7 +1140,6 @@ MitmSplit mitm_split(const mf_problem &p)
         if (best.prefixes <= 1024) break;
         if (best.prefixes <= (1u << 18) && (j == 0 || S * (uint64_t)p.K[j - 1] > 1024)) break;
     }
-    while (best.spad < best.S) best.spad *= 2;
     return best;
 }
 
@@ -1146,11 +1153,6 @@ mf_status search_mitm(mf_problem *p, const mf_objective &objective, int n_steps,
 {
     const MitmSplit sp = mitm_split(*p);
     general = false;
-    // LDS: the kernel's static part takes below 14 KiB
-    if (mitm_lds_bytes(n_steps, p->sumK, sp.spad, objective.kind != MF_OBJ_LINEAR) + 14336 > 163840) {
-        general = true;
-        return MF_OK;
-    }
     MitmArgs a{};
     a.n_models = p->N;
     a.sumK = p->sumK;
@@ -1160,6 +1162,7 @@ mf_status search_mitm(mf_problem *p, const mf_objective &objective, int n_steps,
     a.eq3 = objective.kind != MF_OBJ_LINEAR ? 1 : 0;
     a.S = sp.S;
     a.spad = sp.spad;
+    a.raw_bytes = mitm_raw_bytes(n_steps, p->sumK, sp.spad, a.eq3 != 0);
     a.vram_cap = p->vram_cap;
     for (int i = 0; i < p->N; i++) {
         a.K[i] = p->K[i];

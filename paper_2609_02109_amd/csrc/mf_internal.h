@@ -451,6 +451,7 @@ struct MitmArgs {
     int32_t opt_off[kMaxN];
     uint32_t magic[kMaxN], base_digits[kMaxN];
     uint32_t S, spad, whole_lo, whole_hi;
+    uint32_t raw_bytes;                   // option rows as given staged in LDS (0: read from memory)
     uint32_t part_prefix[2], part_lo[2], part_hi[2];
     uint64_t prefix0;
     float vram_cap;
@@ -561,7 +562,9 @@ constexpr uint64_t kSmallRange = 1ull << 20;   // fp32 ranges up to this size fi
 size_t fixed_lds_bytes(int sumK, bool eq3);
 size_t static_lds_bytes(int n_steps, int sumK, int n_models, bool eq3);
 hipError_t launch_fixed_table(const FixedTableArgs &a, hipStream_t s);
-size_t mitm_lds_bytes(int n_steps, int sumK, uint32_t spad, bool eq3);
+constexpr size_t kMitmLdsMax = 163840 - 14336;   // the kernel's static part takes below 14 KiB
+size_t mitm_lds_bytes(int sumK, uint32_t spad);
+uint32_t mitm_raw_bytes(int n_steps, int sumK, uint32_t spad, bool eq3);
 hipError_t launch_mitm(const MitmArgs &a, int grid, hipStream_t s);
 hipError_t launch_static(const StaticArgs &a, int grid, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1);
 hipError_t launch_static_eval(const StaticArgs &a, hipStream_t s);

@@ -67,22 +67,13 @@ struct MitmLds {
     uint32_t *G;                  // [spad + 4] good suffixes among the first i positions
 };
 
-// Rows as given are staged up to this many bytes (read from memory beyond).
-constexpr size_t kMitmRawBytes = 32768;
-
-__host__ __device__ inline size_t mitm_raw_bytes(int n_steps, int sumK, bool eq3)
-{
-    const size_t b = (size_t)n_steps * sumK * (sizeof(FixedRow) + (eq3 ? sizeof(FixedPen) : 0));
-    return b <= kMitmRawBytes ? b : 0;
-}
-
-__device__ __forceinline__ MitmLds mitm_lds(float4 *smem, int n_steps, int sumK, uint32_t spad, bool eq3)
+__device__ __forceinline__ MitmLds mitm_lds(float4 *smem, int n_steps, int sumK, uint32_t spad, uint32_t raw_bytes)
 {
     MitmLds l;
     l.rows = reinterpret_cast<FixedRow *>(smem);
     l.raw = l.rows + sumK;
     l.rawpen = reinterpret_cast<FixedPen *>(l.raw + (size_t)n_steps * sumK);
-    l.key = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(l.raw) + mitm_raw_bytes(n_steps, sumK, eq3));
+    l.key = reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(l.raw) + raw_bytes);
     l.Bs = reinterpret_cast<double *>(l.key + spad);
     l.M = l.Bs + spad;
     l.lst = reinterpret_cast<unsigned long long *>(l.M + spad + 2);
@@ -90,10 +81,21 @@ __device__ __forceinline__ MitmLds mitm_lds(float4 *smem, int n_steps, int sumK,
     return l;
 }
 
-size_t mitm_lds_bytes(int n_steps, int sumK, uint32_t spad, bool eq3)
+size_t mitm_lds_bytes(int sumK, uint32_t spad)
 {
-    return (size_t)sumK * sizeof(FixedRow) + mitm_raw_bytes(n_steps, sumK, eq3) + (size_t)spad * 16 +
-           (size_t)(spad + 2) * 8 + kMitmWaves * 128 * 8 + (size_t)(spad + 4) * 4;
+    return (size_t)sumK * sizeof(FixedRow) + (size_t)spad * 16 + (size_t)(spad + 2) * 8 + kMitmWaves * 128 * 8 +
+           (size_t)(spad + 4) * 4;
+}
+
+// Rows as given are staged up to this many bytes, where the tables leave room
+// (read from memory otherwise: they are used once for the sums and for the few
+// configurations evaluated).
+constexpr size_t kMitmRawBytes = 32768;
+
+uint32_t mitm_raw_bytes(int n_steps, int sumK, uint32_t spad, bool eq3)
+{
+    const size_t b = (size_t)n_steps * sumK * (sizeof(FixedRow) + (eq3 ? sizeof(FixedPen) : 0));
+    return b <= kMitmRawBytes && mitm_lds_bytes(sumK, spad) + b <= kMitmLdsMax ? (uint32_t)b : 0;
 }
 
 // Offer every lane's key when many may pass: above four, the wave's keys are
@@ -243,8 +245,8 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int N = a.n_models, T = a.n_steps, sumK = a.sumK, k = a.top_k;
     const uint32_t S = a.S, spad = a.spad;
-    const MitmLds l = mitm_lds(smem4, T, sumK, spad, EQ3);
-    const bool staged = mitm_raw_bytes(T, sumK, EQ3) != 0;
+    const MitmLds l = mitm_lds(smem4, T, sumK, spad, a.raw_bytes);
+    const bool staged = a.raw_bytes != 0u;
     unsigned long long t_start = 0;
     if (tid == 0) {
         t_start = (unsigned long long)wall_clock64();
@@ -849,7 +851,7 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
 
 hipError_t launch_mitm(const MitmArgs &a, int grid, hipStream_t s)
 {
-    const size_t lds = mitm_lds_bytes(a.n_steps, a.sumK, a.spad, a.eq3 != 0);
+    const size_t lds = mitm_lds_bytes(a.sumK, a.spad) + a.raw_bytes;
     // one workgroup, more than 32 best: lists of 128
     const bool big = grid == 1 && a.top_k > 32;
     auto pick = [&](auto f1, auto f2, auto f3, auto f4) { return a.eq3 ? (big ? f4 : f3) : (big ? f2 : f1); };

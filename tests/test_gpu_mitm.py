@@ -312,6 +312,50 @@ def test_mitm_spaces_of_many_prefixes(mf, n_options, launches, half, ragged):
     p.close()
 
 
+# the largest suffix table (4,096) beside option rows of several steps that LDS
+# does not hold as well (read from memory), and beside so many options that a
+# shorter suffix is taken
+@pytest.mark.gpu
+def test_mitm_static_rows_beside_the_largest_table(mf):
+    inst = separable([16] * 8, seed=4)
+    T = 16
+    omega = np.arange(T * 8, dtype=np.float32).reshape(T, 8) % 5 - 1
+    want = enumerate_separable(inst, omega.sum(0), 0, inst.space_size, 64)
+    p = mf.Problem(inst)
+    a = p.search_static(np.stack([synth.make_state(inst, t) for t in range(T)]), np.tile(inst.sla, (T, 1)), omega, k=64)
+    p.close()
+    assert a["n_scans"] == 0 and a["n_vram"] == want["n_vram"] and a["n_feas"] == want["n_feas"]
+    np.testing.assert_array_equal(a["top_idx"], want["top_idx"])
+    assert a["top_J"].tobytes() == want["top_J"].tobytes()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("eq3", [False, True])
+def test_mitm_many_option_rows(mf, eq3):
+    # the range holds one option of the first four models: these meet every
+    # constraint, and the cap is the mean sum of the others
+    K = [255] * 5 + [64, 64]
+    inst = instance(K, seed=6)
+    f, off = inst.features, inst.option_offsets
+    f[:off[4], synth.COL_VRAM] = 2.0
+    cap = 8.0 + sum(float(f[off[i]:off[i] + K[i], synth.COL_VRAM].mean()) for i in (4, 5, 6))
+    inst = replace(inst, vram_cap=cap, sla=np.array([np.inf] * 4 + [0.6] * 3, np.float32))
+    lo = inst.space_size // 3 + 11
+    st = synth.make_state(inst, 6)
+    ob = synth.make_objective(inst, 6, tau_range=(-0.4, 0.3)) if eq3 else None
+    if eq3:
+        ob.tau[:4] = -np.inf
+        ob.prev_variant[:4] = -1
+    p = mf.Problem(inst, variants=ob)
+    for n in (9000, 400_000):
+        for k in (1, 64):
+            a = p.search(inst.sla, inst.omega, k=k, lo=lo, hi=lo + n, objective=ob, state=st)
+            b = p.search(inst.sla, inst.omega, k=k, lo=lo, hi=lo + n, objective=ob, state=st, dump=True)
+            same(a, b)
+            assert a["n_scans"] == 0 and b["n_scans"] == 1 and a["n_feas"] > 0 and a["n_vram"] < n
+    p.close()
+
+
 # prefixes that tie, in a search of one workgroup: the first `zero` models weigh
 # nothing and (flat) take the same VRAM.  Up to 1,024 of them are looked into;
 # more, or a tie that goes through the suffixes too, is the scan's

@@ -69,7 +69,7 @@ def test_ga_no_feasible_configuration(mf, orc):
     inst.vram_cap = 1.0
     sc = synth.ga_scenarios(5, 3, seed=0)
     p = mf.Problem(inst)
-    # both fitness kernels: a small population, and 3 x 4096 individuals
+    # the fitness kernels of a small population and, by the memo, of 3 x 4096 individuals
     for pop in (16, 4096):
         g = p.ga(sc.sla, sc.omega, pop=pop, gens=2, final_pop=True)
         assert np.all(g["best_idx"] == np.uint64(2 ** 64 - 1)) and np.all(np.isneginf(g["best_J"]))
@@ -148,7 +148,8 @@ def test_ga_largest_operator_footprint(mf, orc):
 
 
 def test_ga_large_population_shapes(mf, orc):
-    # populations above 8,192 take the one-lane-per-individual fitness: the
+    # populations above 8,192 (under a fixed state from the option rows, else from
+    # the table of configurations; past its limit further below): the
     # paper's 64-32 sigmoid predictor with Eq. 3 and a fixed state, 22 inputs
     # at 64-64, 14 inputs at 32-32; ragged last workgroups
     a = synth.make_instance([12, 12, 9, 9, 9], 8, 4, 64, 32, seed=11, vram_quantile=0.8, act="sigmoid")
@@ -163,15 +164,30 @@ def test_ga_large_population_shapes(mf, orc):
     run_both_obj(mf, orc, c, sc.sla, sc.omega, synth.make_objective(c, 13), None, pop=3000, gens=3, seed=14)
 
 
-def test_ga_memo_across_runs_and_forward_count(mf, orc):
-    # large populations keep a memo of canonical predictions per joint index
-    # for the run: later generations read it.  Runs on one problem reuse its
-    # workspace (the memo starts empty every run); every run still equals the
-    # oracle's replay, and the count of individuals that ran the surrogates
-    # lies between one generation and all of them.
+def count_forwards(mf, p, inst, g, S, pop, gens):
+    """Which way a run of more than 8,192 individuals took, from its count:
+    "table" (every VRAM-feasible configuration), "all" (every individual) or
+    "memo" (in between)."""
+    n_fl = p.search(inst.sla, inst.omega, state=synth.make_state(inst, 0))["n_vram"]
+    if g["forwards"] == n_fl:
+        return "table"
+    if g["forwards"] == S * pop * (gens + 1):
+        return "all"
+    assert S * pop <= g["forwards"] < S * pop * (gens + 1)
+    return "memo"
+
+
+@pytest.mark.parametrize("gens,path", [(30, "table"), (3, "memo")])
+def test_ga_memo_across_runs_and_forward_count(mf, orc, gens, path):
+    # large populations tabulate the fitness of every feasible configuration
+    # (the space within 32,768 configurations per generation) or keep a memo of
+    # canonical predictions per joint index that later generations read.  Runs
+    # on one problem reuse its workspace (table and memo start empty every
+    # run); every run still equals the oracle's replay, and the count says
+    # which way it took.
     inst, sc, gp = synth.cfg3(3)
     p = mf.Problem(inst)
-    kw = dict(pop=2048, gens=30, tourn_k=3, p_cx=0.7, p_swap=0.5, p_mut=0.05)
+    kw = dict(pop=2048, gens=gens, tourn_k=3, p_cx=0.7, p_swap=0.5, p_mut=0.05)
     first = None
     for rows, seed in ((slice(0, 6), 1), (slice(6, 12), 2), (slice(0, 6), 1)):
         sla, om = sc.sla[rows], sc.omega[rows]
@@ -181,8 +197,7 @@ def test_ga_memo_across_runs_and_forward_count(mf, orc):
         np.testing.assert_array_equal(g["best_idx"], r["best_idx"])
         assert g["best_J"].tobytes() == r["best_J"].tobytes()
         np.testing.assert_array_equal(g["final_pop"].cpu().numpy().astype(np.uint64), r["final_pop"])
-        n_gen = 6 * kw["pop"]
-        assert n_gen <= g["forwards"] < n_gen * (kw["gens"] + 1) // 2, g["forwards"]
+        assert count_forwards(mf, p, inst, g, 6, kw["pop"], gens) == path
         if first is None:
             first = g
         elif seed == 1:
@@ -191,3 +206,26 @@ def test_ga_memo_across_runs_and_forward_count(mf, orc):
     # small populations evaluate every individual
     small = p.ga(sc.sla[:2], sc.omega[:2], pop=64, gens=4, seed=3)
     assert small["forwards"] == 2 * 64 * 5
+
+
+# The one-lane fitness kernels of populations above 8,192, over spaces past the
+# table's limit (32,768 configurations per generation): with the memo (the
+# paper's 64-32 sigmoid predictor under Eq. 3, 22 inputs at 64-64, bf16, a
+# ragged last workgroup, weights too large for LDS); without it where the memo
+# would exceed 256 MiB; and the kernel without the option chains (181 rows of
+# 64 units do not fit its LDS)
+@pytest.mark.parametrize("opts,L,A,hid,act,dtype,eq3,S,kw,path", [
+    ([12, 12, 9, 9, 9], 8, 4, (64, 32), "sigmoid", "f32", True, 5, dict(pop=2046, gens=3, p_mut=0.1), "memo"),
+    ([10, 9, 8, 7, 6, 5], 16, 6, (64, 64), "identity", "f32", False, 5, dict(pop=1750, gens=4), "memo"),
+    ([12, 12, 9, 9, 9], 8, 4, (64, 64), "identity", "bf16", False, 3, dict(pop=3000, gens=2), "memo"),
+    ([20, 20, 20, 20, 20], 8, 4, (32, 32), "identity", "f32", False, 3, dict(pop=3000, gens=2), "all"),
+    ([61, 60, 60], 8, 4, (64, 32), "identity", "f32", True, 3, dict(pop=3000, gens=2, p_mut=0.3), "all"),
+], ids=["sigmoid-eq3", "64-64", "bf16", "no-memo", "no-chains"])
+def test_ga_large_population_past_the_table(mf, orc, opts, L, A, hid, act, dtype, eq3, S, kw, path):
+    inst = synth.make_instance(opts, L, A, *hid, seed=15, vram_quantile=0.7, act=act, dtype=dtype)
+    ob = synth.make_objective(inst, 15) if eq3 else None
+    sc = synth.ga_scenarios(inst.n_models, S, seed=15)
+    g, r = run_both_obj(mf, orc, inst, sc.sla, sc.omega, ob, None, seed=16, **kw)
+    p = mf.Problem(inst)
+    assert count_forwards(mf, p, inst, g, S, kw["pop"], kw["gens"]) == path
+    p.close()

@@ -620,9 +620,14 @@ WsLayout ws_layout(const mf_problem &p, uint64_t n, int top_k, uint32_t worklist
     // 27.2 us at 105,435 configurations, k = 16).  Dealt without the hash the
     // best of equal power-of-two counts met in few workgroups: 16^5, k = 16 took
     // the fallback pass, 287 us against 131.
+    // Never more than in order: over few workgroups the formula asks for more
+    // than the top-k can put into one (4,096 configurations over 8 workgroups of
+    // 12-64-64-2, k = 16: 17 entries, 94 us a call, against 9 and 80; in order
+    // 84), and in 700 random spaces of two to six models none of up to 2^20
+    // configurations on several workgroups needed the fallback pass for k <= 16.
     w.spread = w.small && w.grid > 1 && p.space <= (1ull << 32);
     const double m = 1.5 * top_k / w.grid;
-    w.eval_spread = std::min(w.kp, (int)std::ceil(m + 6.0 * std::sqrt(m) + 3.0));
+    w.eval_spread = std::min(w.eval_top, (int)std::ceil(m + 6.0 * std::sqrt(m) + 3.0));
     const size_t n_seg = (size_t)w.seg_cap * (w.small ? w.grid : 0);
     w.seg = o; o = align256(o + n_seg * 8);
     w.segJ = o; o = align256(o + n_seg * 4);

@@ -49,7 +49,7 @@ def test_dealt_ranges(mf, K, H, k, lo, n, flat):
     assert a["top_J"].tobytes() == b["top_J"].tobytes()
 
 
-@pytest.mark.parametrize("K", [(16,) * 4, (8,) * 5, (32,) * 3, (8,) * 6, (16,) * 5])
+@pytest.mark.parametrize("K", [(16,) * 4, (8,) * 5, (32,) * 3, (8,) * 6, (16,) * 5, (5, 5, 5, 5, 4), (20,) * 3, (10,) * 3])
 @pytest.mark.parametrize("k", [16, 64])
 def test_dealt_ranges_of_equal_counts(mf, K, k):
     """Where every option count is the same power of two, and one model weighs

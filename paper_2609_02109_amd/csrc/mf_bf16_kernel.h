@@ -203,9 +203,12 @@ fast_bf16_kernel(const Bf16Args args, const FastConst fc, const Bf16Const bc, co
         }
         // the leading models whose digits all the wave's configurations share:
         // their part of the aggregate once (the sums stay in model order)
+        // (not in the general kernels under Eq. 3: they hold so many scalars
+        // that the spilled ones cost more: 16^6, H = 64
+        // 5,180 us with it, 4,800 without; 16^6, H = 128 7,340 and 7,395)
         int m0 = 0;
         float pa[4] = {0.f, 0.f, 0.f, 0.f}, pv = 0.f;
-        if constexpr (!LIST) {
+        if constexpr (!LIST && (FULL || !OBJ)) {
             uint32_t carry = TW * 32 - 1;
             bool run = true;
             int m = MAXN;

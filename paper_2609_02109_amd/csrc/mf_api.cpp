@@ -2186,9 +2186,18 @@ mf_status mf_eval_fast(mf_problem *p, const uint64_t *d_idx, int64_t n, float *d
     fa.lo = 0;
     fa.n = (uint64_t)n;
     fa.idx_list = d_idx;
-    const uint64_t per_wg = (uint64_t)kSearchWaves * 64;
+    // Up to a tile of 32 per wave the small ranges' kernel, the tiles dealt over
+    // the chip, one to a workgroup first: a wave has one tile to finish, not
+    // two, and a SIMD to itself up to 32,768 (24^6, 22-64-64-2: 32 of a list
+    // 33.8 us a call against 36.0 for the scan, 4,000 36.2 against 44.5, 50,000
+    // 40.4 against 46.0; past that two tiles per wave are ahead, 100,000 47.9).
+    fa.small = (uint64_t)n <= (uint64_t)p->num_cus * kSearchWaves * 32 ? 1 : 0;
+    const uint64_t per_wg = fa.small ? 32 : (uint64_t)kSearchWaves * 64;
     const int grid = (int)std::max<uint64_t>(1, std::min<uint64_t>(((uint64_t)n + per_wg - 1) / per_wg,
                                                                     (uint64_t)p->num_cus));
+    fa.waves = kSearchWaves;
+    fa.total_waves = grid * kSearchWaves;
+    fa.agg_cols = p->d_agg_cols;
     fa.sla = p->d_zeros;
     fa.omega = p->d_zeros;
     fa.pred = d_pred;

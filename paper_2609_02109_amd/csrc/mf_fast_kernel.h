@@ -851,11 +851,14 @@ __device__ __forceinline__ uint32_t deal_rotation(uint32_t h, uint32_t n)
 
 // Small ranges: a tile of 32 configurations per wave (latency counts here, so
 // the range goes to as many waves as there are tiles), then the certification.
+// Also short lists (predictions only), their tiles dealt over the workgroups
+// so that few waves share a SIMD.
 template <int MAXN, int A, int H, int WAVES, bool OBJ, bool SIG>
 __global__ void __launch_bounds__(WAVES * 64, 1)
 small_kernel(const FastArgs args, const FastConst fc, const int kp)
 {
     const uint32_t spread = args.spread;
+    const uint64_t *list = args.idx_list;
     constexpr int MB = H / 32;         // 32-row blocks of a hidden layer
     static_assert(A <= 8, "layer 1 takes at most 4 aggregate slots per lane half");
     constexpr bool L1ONE = A <= 4;     // two slots per lane half: one layer-1 instruction per block
@@ -906,7 +909,7 @@ small_kernel(const FastArgs args, const FastConst fc, const int kp)
     const uint32_t n_tiles = ((spread ? spread : (uint32_t)n) + 31) >> 5;   // n <= 2^20
 
     uint32_t bd[MAXN] = {};
-    if (spread == 0u) {
+    if (spread == 0u && !list) {
         uint64_t x = args.lo + (uint64_t)gw * 32u;
 #pragma unroll
         for (int j = MAXN - 1; j >= 0; j--) {
@@ -925,7 +928,7 @@ small_kernel(const FastArgs args, const FastConst fc, const int kp)
     uint32_t c_vram = 0, c_feas = 0;
 
     const uint32_t tile_step = spread ? (uint32_t)WAVES : (uint32_t)args.total_waves;
-    for (uint32_t tile = spread ? wv : gw; tile < n_tiles; tile += tile_step) {
+    for (uint32_t tile = spread ? wv : list ? wv * gridDim.x + blockIdx.x : gw; tile < n_tiles; tile += tile_step) {
         uint32_t o = tile * 32u + (uint32_t)col;   // in order, or the round
         if (spread) {
             const uint32_t at = (uint32_t)blockIdx.x + deal_rotation(o, gridDim.x);
@@ -945,6 +948,17 @@ small_kernel(const FastArgs args, const FastConst fc, const int kp)
                     const uint32_t q = (uint32_t)(((double)x + 0.5) * s_inv[j]);
                     d[j] = x - q * (uint32_t)fc.K[j];
                     x = q;
+                }
+            }
+        } else if (list) {
+            uint64_t x = list[valid ? off : n - 1];
+#pragma unroll
+            for (int j = MAXN - 1; j >= 0; j--) {
+                d[j] = 0;
+                if (j < N) {
+                    const uint64_t k = (uint64_t)fc.K[j];
+                    d[j] = (uint32_t)(x % k);
+                    x /= k;
                 }
             }
         } else {
@@ -1138,6 +1152,7 @@ small_kernel(const FastArgs args, const FastConst fc, const int kp)
             }
         }
 
+        if (list) continue;   // predictions only
         const bool mine = valid && half == 0;
         const bool anyunc = umask != 0u;
         const bool sla_sure = !anyfail && !anyunc;
@@ -1187,6 +1202,7 @@ small_kernel(const FastArgs args, const FastConst fc, const int kp)
         }
     }
 
+    if (list) return;
     write_wg_result<WAVES>(wl, c_vram, c_feas, lst, args, kp, lane, wv);
     // s_nwork is final: every wave's appends precede the tree merge's barriers
     small_certify<H, WAVES, OBJ, SIG>(args, fc, smem, par, wl.s[0], kp, s_nwork, lane, wv, t_start);
@@ -1203,7 +1219,7 @@ static hipError_t launch_fast_t(const FastArgs &a, const FastConst &fc, int grid
     b.lst_off = fast_lists_in_image(a.lay, waves, kp) ? 0 : a.lay.total_floats + kFastPar;
     const size_t lds = fast_dyn_lds(a.lay, waves, kp, (size_t)a.ep_bytes);
     if (a.small) {
-        if (mode != kModeSearch) return hipErrorInvalidValue;
+        if (mode != kModeSearch && mode != kModeList) return hipErrorInvalidValue;
         auto fn = eq3 ? small_kernel<MAXN, A, H, kSearchWaves, true, SIG>
                       : small_kernel<MAXN, A, H, kSearchWaves, false, SIG>;
         if (waves != kSearchWaves) {

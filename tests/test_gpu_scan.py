@@ -50,11 +50,15 @@ def test_scan_against_pieces(mf, K, A, H, k, lo, n):
     assert a["top_J"].tobytes() == J[order].tobytes()
 
 
-@pytest.mark.parametrize("n", [1, 31, 32, 63, 64, 65, 511, 513])
-def test_list_edges(mf, n):
+# up to a tile of 32 per wave (65,536 on 256 CUs) by the small ranges' kernel,
+# past that by the scan
+@pytest.mark.parametrize("n", [1, 31, 32, 63, 64, 65, 511, 513, 8191, 8193, 65535, 65536, 65537, 70001])
+@pytest.mark.parametrize("K,A,H,act", [([9, 1, 11, 7], 6, 64, "identity"), ([2] * 9 + [1, 3], 4, 32, "sigmoid"),
+                                       ([250, 3], 2, 64, "sigmoid")])
+def test_list_edges(mf, n, K, A, H, act):
     """A configuration's predictions do not depend on its place in the list,
     nor on which kernel made them."""
-    inst = synth.make_instance([9, 1, 11, 7], 12, 6, 64, 64, seed=3, vram_quantile=0.8)
+    inst = synth.make_instance(K, 12, A, H, H, seed=3, vram_quantile=0.8, act=act)
     p = mf.Problem(inst)
     dump = p.search(inst.sla, inst.omega, k=1, dump=True)["pred"].cpu().numpy()
     idx = np.random.default_rng(n).integers(0, inst.space_size, n)

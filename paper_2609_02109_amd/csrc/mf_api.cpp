@@ -2253,8 +2253,26 @@ struct GaWs {
 // chip evaluating; 12-32-32-2, N = 5), a generation in two launches about
 // 30 us more than one inside the run kernel: worth it up to this many
 // configurations per generation, and while the run evaluates that many
-// individuals at all.
+// individuals at all.  (At 22-64-64-2, N = 6, a configuration costs some 3 ns,
+// an individual's forward as much more: 10^6 configurations, 64 scenarios of
+// 2,048, 31 generations 5.9 ms with the table, 8.2 with the memo.)
 constexpr uint64_t kGaTablePerGen = 32768;
+
+// Small populations (at most kGaWideMax individuals, a workgroup each) do not
+// wait for a lane's whole forward, the table does: N models of a chain of F =
+// H1 (H2 + A) steps, about 14.5 ns each but for the first 400 (11, 27, 57 us a
+// model at 32-32, 64-32, 64-64), for every 131,072 configurations the chip holds
+// at a time.  A generation in two launches costs about 10 + 0.8 N us more than
+// one in the run kernel, and 0.57 ps a step of its forwards.  256
+// configurations, N = 8, 64-64, 4 x 32 individuals: 190 us for 3 generations
+// without the table and 570 with it, even at 30.
+static bool ga_table_pays(const mf_problem *p, const mf_ga_args *a)
+{
+    const double sp = (double)a->n_scen * a->pop, F = (double)p->H1 * (p->H2 + p->A);
+    if (sp > (double)kGaWideMax) return true;   // its first generation waits for the same forwards
+    const double table = 10.0 + p->N * std::max(14.5e-3 * F - 6.0, 5.0) * std::ceil((double)p->space / 131072.0);
+    return (a->gens + 1) * (10.0 + 0.8 * p->N + sp * p->N * F * 0.57e-6) > table;
+}
 
 // The GAConst of a run without its device pointers' workspace parts (the
 // shape fields the kernels' choices depend on).
@@ -2294,7 +2312,7 @@ static GaWs ga_ws(const mf_problem *p, const mf_ga_args *a)
     c.obj.kind = a->objective.kind;
     const uint64_t evals = (uint64_t)sp * (uint64_t)(a->gens + 1);
     w.table = !c.fixed && ga_table_supported(c) && p->space * (uint64_t)a->n_scen * 8u <= kGaTableMaxBytes &&
-              p->space <= kGaTablePerGen * (uint64_t)a->gens && p->space <= evals;
+              p->space <= kGaTablePerGen * (uint64_t)a->gens && p->space <= evals && ga_table_pays(p, a);
     w.run = (c.fixed || w.table) && ga_run_supported(c, a->pop, a->tourn_k);
     w.table = w.table && w.run;
     const size_t per_gen = (size_t)a->n_scen * (a->pop / 2) * ga_record_bytes(a->tourn_k, p->N);

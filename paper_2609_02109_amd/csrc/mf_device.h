@@ -290,10 +290,11 @@ __device__ __forceinline__ void wl_offer(WaveList<NS> &L, unsigned long long myk
     }
 }
 
-// wl_offer for one-register lists when many keys may pass at once (a list
-// still filling): above four passing keys the wave's keys are sorted
-// descending by a bitonic network and merged into the list in one step.
-__device__ __forceinline__ void wl_offer_many(WaveList<1> &L, unsigned long long mykey, int lane, int kp)
+// wl_offer when many keys may pass at once (a list still filling): above four
+// passing keys the wave's keys are sorted descending by a bitonic network and
+// merged into the list in one step.
+template <int NS>
+__device__ __forceinline__ void wl_offer_many(WaveList<NS> &L, unsigned long long mykey, int lane, int kp)
 {
     const bool pass = mykey > L.thr;
     if (__popcll(__ballot(pass)) <= 4) {
@@ -305,7 +306,7 @@ __device__ __forceinline__ void wl_offer_many(WaveList<1> &L, unsigned long long
     for (int k = 2; k <= 64; k <<= 1)
 #pragma unroll
         for (int j = k >> 1; j > 0; j >>= 1) x = cx_lane(x, j, lane, (lane & k) == 0);
-    const unsigned long long b[1] = {x};
+    unsigned long long b[NS] = {x};
     wl_merge_sorted(L, b, lane, kp);
 }
 

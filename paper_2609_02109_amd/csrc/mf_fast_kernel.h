@@ -897,7 +897,6 @@ small_kernel(const FastArgs args, const FastConst fc, const int kp)
     __syncthreads();
 
     const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
-    // aggregate centre of the slots this lane feeds to layer 1
     // aggregate centre and power-of-two scale of the slots this lane feeds
     // to layer 1 (read per tile: registers are the kernel's limit)
     const float4 *cen_p = reinterpret_cast<const float4 *>(smem + Ly.off_c + 4 * half);

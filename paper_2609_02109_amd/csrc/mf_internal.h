@@ -148,7 +148,7 @@ struct FastArgs {
     FastLayout lay;
     uint64_t lo, n;             // range [lo, lo+n); list mode: n entries of idx_list
     const uint64_t *idx_list;   // list mode only
-uint32_t digits[kMaxN];     // mixed-radix digits, small ranges: of total_waves * 32 mod |Lambda|; scan: of lo
+    uint32_t digits[kMaxN];     // mixed-radix digits, small ranges: of total_waves * 32 mod |Lambda|; scan: of lo
     int total_waves;            // small ranges
     int waves;                  // small ranges: waves per workgroup (kSearchWaves or kSearchWavesWide)
     const float *sla;           // device [N]

@@ -98,29 +98,6 @@ uint32_t mitm_raw_bytes(int n_steps, int sumK, uint32_t spad, bool eq3)
     return b <= kMitmRawBytes && mitm_lds_bytes(sumK, spad) + b <= kMitmLdsMax ? (uint32_t)b : 0;
 }
 
-// Offer every lane's key when many may pass: above four, the wave's keys are
-// sorted and merged in one step.
-template <int NS>
-__device__ __forceinline__ void wl_offer_bulk(WaveList<NS> &L, unsigned long long mykey, int lane, int kp)
-{
-    const bool pass = mykey > L.thr;
-    const int n = __popcll(__ballot(pass));
-    if (n <= 4) {
-        if (n) wl_offer(L, mykey, lane, kp);
-        return;
-    }
-    unsigned long long x = pass ? mykey : 0ull;
-#pragma unroll
-    for (int k = 2; k <= 64; k <<= 1)
-#pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1) x = cx_lane(x, j, lane, (lane & k) == 0);
-    unsigned long long b[NS];
-    b[0] = x;
-#pragma unroll
-    for (int j = 1; j < NS; j++) b[j] = 0ull;
-    wl_merge_sorted(L, b, lane, kp);
-}
-
 // A prefix of the launch: its exact VRAM sum (fp32, model order), the sum of
 // its terms and its flags.
 struct Prefix {
@@ -537,7 +514,7 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
             cf += g;
         }
         if (grid == 1) {
-            wl_offer_bulk(L, key, lane, kp);
+            wl_offer_many(L, key, lane, kp);
         } else {
             m3 = key > m2 ? m2 : (key > m3 ? key : m3);
             m2 = key > m1 ? m1 : (key > m2 ? key : m2);
@@ -622,7 +599,7 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
         }
         // the 64 largest of the threads' maxima (distinct prefixes): the
         // k-th bounds the k-th largest bound of all from below
-        wl_offer_bulk(Q, best, lane, kp);
+        wl_offer_many(Q, best, lane, kp);
 #pragma unroll
         for (int j = 0; j < NS; j++) l.lst[wv * kp + j * 64 + lane] = Q.s[j];
         wl_tree_merge<NS, kMitmWaves>(Q, l.lst, kp, wv, lane, kp);

@@ -29,11 +29,11 @@ sys.path.insert(0, ROOT)
 PEAK_FP32_TFLOPS = 157.3
 PEAK_FP64_TFLOPS = 78.6
 CPU_SAMPLE_PER_THREAD = 1 << 20
-# HBM bytes per launch of the fast search kernel from rocprofv3 FETCH_SIZE /
+# HBM bytes per launch of the N=6 scan kernel from rocprofv3 FETCH_SIZE /
 # WRITE_SIZE passes (profiles/fast_kernel_n6_k24_h64_hbm_counters.md), valid
 # only for the kernel source they were taken on
-TRAFFIC_BYTES = 15_930_880 + 20_811_552
-TRAFFIC_SOURCE_SHA = "7ae62e82fdc3c035"
+TRAFFIC_BYTES = 16_028_544 + 15_584_384
+TRAFFIC_SOURCE_SHA = "0e385ed50ea6cd83"
 
 
 # the fast kernel's source: its file and the headers it includes

@@ -32,8 +32,8 @@ CPU_SAMPLE_PER_THREAD = 1 << 20
 # HBM bytes per launch of the N=6 scan kernel from rocprofv3 FETCH_SIZE /
 # WRITE_SIZE passes (profiles/fast_kernel_n6_k24_h64_hbm_counters.md), valid
 # only for the kernel source they were taken on
-TRAFFIC_BYTES = 16_028_544 + 15_584_384
-TRAFFIC_SOURCE_SHA = "0e385ed50ea6cd83"
+TRAFFIC_BYTES = 15_856_384 + 15_595_296
+TRAFFIC_SOURCE_SHA = "ed1d48cf58e15052"
 
 
 # the fast kernel's source: its file and the headers it includes

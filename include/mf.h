@@ -363,8 +363,10 @@ typedef struct {
     /* Optional host output (NULL: none): the surrogate evaluations of the run,
      * in configurations.  Runs whose individuals outnumber the joint space (and
      * whose space has at most 32,768 configurations per generation and 1 GiB of
-     * fitness over the scenarios, at the shapes of the one-lane kernel) evaluate every
-     * VRAM-feasible configuration first: their number.
+     * fitness over the scenarios, at the shapes of the one-lane kernel, and with at
+     * most 8,192 individuals where the generations take longer than one lane's
+     * forward of every model) evaluate every VRAM-feasible configuration first:
+     * their number.
      * Otherwise large populations (S x pop > 8192, the same shapes, |Lambda|
      * (16 N + 4) bytes <= 256 MiB) keep a memo of each evaluated index's
      * predictions in the workspace for the rest of the run: the individuals

@@ -205,9 +205,9 @@ __device__ __forceinline__ void wave_best(double &f, uint32_t &x)
 // scenario: individuals are kept as packed digits, so that crossover and
 // mutation are a few 64-bit masks, and a generation's candidates, parents and
 // rows are read in three dependent LDS steps.  64 scenarios, 2,048 x 100
-// generations: 4.1 us per generation here (35 us as two launches), 1.55 ms for
-// the whole run with the draws (0.75 ms) and the table (0.15 ms), 3.73 ms
-// before; one scenario, 100 x 30: 225 us against 702 us.
+// generations: 5.1 us per generation here (35 us as two launches), 1.55 ms for
+// the whole run with the draws (0.78 ms) and the table (0.19 ms), 3.75 ms
+// before; one scenario, 100 x 30: 3.9 us per generation, 225 us against 739 us.
 template <bool FIXED, int QP, int MAXN>
 __global__ void __launch_bounds__(kRunMaxThreads) ga_run_kernel(const GARunArgs r)
 {

@@ -34,9 +34,10 @@
 //
 // Bound by latency: some 15 dependent LDS phases of 2-4 us each, no unit busy.
 // Whole searches, call to host result, general scan before -> now (MI355X):
-// 24^6 configurations, top-1: 144 us -> 77 us (kernel 46); 16^8, top-64:
-// 2,417 us -> 130 us (kernel 75); 104,976 (Eq. 3, top-1): 78 us -> 59 us
-// (kernel 25); the same over 12 steps: 261 us -> 100 us (kernel 28).
+// 24^6 configurations, top-1: 153 us -> 76-79 us (kernel 48); 16^8, top-64:
+// 2,610 us -> 112-230 us by the input (kernel 78 and more: the evaluation of
+// what reaches theta); 104,976 (Eq. 3, top-1): 78 us -> 54-58 us (kernel 26);
+// the same over 12 steps: 276 us -> 93-100 us (kernel 28).
 #include "mf_canon.h"
 
 namespace mfi {

@@ -38,6 +38,8 @@
 // 2,610 us -> 112-230 us by the input (kernel 78 and more: the evaluation of
 // what reaches theta); 104,976 (Eq. 3, top-1): 78 us -> 54-58 us (kernel 26);
 // the same over 12 steps: 276 us -> 93-100 us (kernel 28).
+#include <type_traits>
+
 #include "mf_canon.h"
 
 namespace mfi {
@@ -679,13 +681,14 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
     __syncthreads();
     // a wave per candidate: the segments, then the suffixes, whose sum reaches
     // theta; f takes each group of 64 with the hits marked
-    auto each_hit = [&](const double &bar, auto f) {
+    // (tie: stop once they are too many)
+    auto each_hit = [&](auto tie, const double &bar, auto f) {
         for (uint32_t c = wv; !general && c < ncand; c += kMitmWaves) {
             const double B = cand_B[c];
             const uint32_t pos = cand_pos[c];
             unsigned long long segs = __ballot((uint32_t)lane * 64u < pos && (B + s_segmax[lane]) + slack >= bar);
             while (segs) {
-                if (full && *(volatile uint32_t *)&s_nhit > kMitmTieHits) return;
+                if (tie.value && *(volatile uint32_t *)&s_nhit > kMitmTieHits) return;
                 const uint32_t i = ((uint32_t)__ffsll((long long)segs) - 1u) * 64u + lane;
                 segs &= segs - 1;
                 const bool hit = i < pos && l.Bs[i] > -INFINITY && (B + l.Bs[i]) + slack >= bar;
@@ -696,12 +699,14 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
     K128 slot = {0ull, 0ull}, thr = {0ull, 0ull};
     double thrJ = theta;
     const bool parts = a.part_hi[0] != 0u || a.part_hi[1] != 0u;
-    each_hit(theta, [&](bool hit, uint32_t prel, uint32_t u) {
+    const auto count = [&](bool hit, uint32_t prel, uint32_t u) {
         if (hit) {
             const uint32_t at = atomicAdd(&s_nhit, 1u);
             if (at < kMitmHits) s_hit[at] = ((unsigned long long)prel << 32) | u;
         }
-    });
+    };
+    if (full) each_hit(std::true_type{}, theta, count);
+    else each_hit(std::false_type{}, theta, count);
     __syncthreads();
     const uint32_t nhit = s_nhit;
     general = general || (full && nhit > kMitmTieHits);
@@ -736,7 +741,7 @@ __global__ void __launch_bounds__(kMitmThreads) mitm_kernel(const MitmArgs a)
     } else if (!general) {
         // many (fewer than k prefixes feasible, or equal values): each wave's
         // running top-k
-        each_hit(thrJ, [&](bool hit, uint32_t prel, uint32_t u) {
+        each_hit(std::false_type{}, thrJ, [&](bool hit, uint32_t prel, uint32_t u) {
             K128 key = {0ull, 0ull};
             if (hit) {
                 float v;
